@@ -95,6 +95,16 @@ __device__ __forceinline__ void add_global(unsigned long long* p, unsigned long 
 }
 __device__ __forceinline__ void add_global(float* p, float v) { unsafeAtomicAdd(p, v); }
 
+// LDS windows of the tiled deposits: integer weights are summed as they are,
+// float weights in FP64 (the f32 LDS add is 20 times slower than the f64 one,
+// and the window sum then rounds once, when it is added to the mesh).
+template <typename T>
+using win_t = typename std::conditional<std::is_same<T, float>::value, double, T>::type;
+__device__ __forceinline__ void add_window(unsigned long long* p, unsigned long long v) {
+  atomicAdd(p, v);
+}
+__device__ __forceinline__ void add_window(double* p, float v) { unsafeAtomicAdd(p, (double)v); }
+
 template <int LOGN, typename T>
 __device__ __forceinline__ void deposit_global(T* __restrict__ mass, int ix, int iy, int iz,
                                                const T w[8]) {

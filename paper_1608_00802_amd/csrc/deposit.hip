@@ -89,7 +89,10 @@ __global__ void __launch_bounds__(kBlock) k_deposit_f32(const float* __restrict_
 // the +1 faces CIC reaches), then adds the window to the mesh with one global
 // atomic per non-zero cell.  Particles that left their tile since the sort
 // deposit with global atomics directly, so the result never depends on how
-// well sorted the particles are.
+// well sorted the particles are.  The float form sums its window in FP64
+// (win_t): an LDS add of f32 takes 194 cycles per wave instruction on gfx950
+// and one of f64 9.5 (conflict-free; u64: 7.3): 108 -> 24 us for this kernel
+// at 128^3 with 128^3 particles, 124 -> 40 us for the fused gather-deposit.
 // Threads per block of the tiled deposit: its 34 KB window leaves room for
 // four blocks per CU, so 512-thread blocks fill all 32 wave slots.
 constexpr int kDepBlock = 512;
@@ -99,13 +102,14 @@ __global__ void __launch_bounds__(kDepBlock) k_deposit_tiled(const void* __restr
                                                           int64_t np, TileMap tm,
                                                           void* __restrict__ mass_v, Batch bt) {
   using T = typename std::conditional<FIXED, unsigned long long, float>::type;
+  using A = win_t<T>;
   constexpr int N = 1 << LOGN;
   constexpr int MASK = N - 1;
   constexpr int TX = 1 << tile_lx(LOGN), TY = 1 << tile_ly(LOGN), TZ = 1 << tile_lz(LOGN);
   constexpr int HD = kDepHalo;   // window: cells o - HD .. o + T + HD
   constexpr int WX = TX + 1 + 2 * HD, WY = TY + 1 + 2 * HD, WZ = TZ + 1 + 2 * HD;
   constexpr int NTY = N / TY, NTZ = N / TZ;
-  __shared__ T acc[WX * WY * WZ];
+  __shared__ A acc[WX * WY * WZ];
   const int sl = bslot(bt);
   pos = poff(pos, bt, sl);
   T* mass = woff(static_cast<T*>(mass_v), bt, sl);
@@ -115,7 +119,7 @@ __global__ void __launch_bounds__(kDepBlock) k_deposit_tiled(const void* __restr
   unsigned lo, hi;
   if (!chunk_of(tm, t, lo, hi)) return;
   const int ox = (t / (NTY * NTZ)) * TX, oy = ((t / NTZ) % NTY) * TY, oz = (t % NTZ) * TZ;
-  for (int c = threadIdx.x; c < WX * WY * WZ; c += kDepBlock) acc[c] = (T)0;
+  for (int c = threadIdx.x; c < WX * WY * WZ; c += kDepBlock) acc[c] = (A)0;
   __syncthreads();
   for (unsigned i = lo + threadIdx.x; i < hi; i += kDepBlock) {
     int ix, iy, iz;
@@ -131,14 +135,14 @@ __global__ void __launch_bounds__(kDepBlock) k_deposit_tiled(const void* __restr
     if (rx < TX + 2 * HD && ry < TY + 2 * HD && rz < TZ + 2 * HD) {
 #pragma unroll
       for (int c = 0; c < 8; ++c)
-        atomicAdd(&acc[((rx + (c >> 2)) * WY + ry + ((c >> 1) & 1)) * WZ + rz + (c & 1)], w[c]);
+        add_window(&acc[((rx + (c >> 2)) * WY + ry + ((c >> 1) & 1)) * WZ + rz + (c & 1)], w[c]);
     } else {
       deposit_global<LOGN>(mass, ix, iy, iz, w);
     }
   }
   __syncthreads();
   for (int c = threadIdx.x; c < WX * WY * WZ; c += kDepBlock) {
-    const T v = acc[c];
+    const T v = (T)acc[c];
     if (v != (T)0) {
       const int lx = c / (WY * WZ), ly = (c / WZ) % WY, lz = c % WZ;
       const size_t cell = ((size_t)((ox - HD + lx) & MASK) * N + ((oy - HD + ly) & MASK)) * N +

@@ -363,7 +363,7 @@ __global__ void __launch_bounds__(kGatherBlock, gather_waves(WIDE, EN && HAS_Q))
   __shared__ float win[WX * WY * WZ];
   // energy form: win holds phi and winq holds Q (interpolated separately)
   __shared__ float winq[EN && HAS_Q ? WX * WY * WZ : 1];
-  __shared__ T dacc[DEP ? DX * DY * DZ : 1];
+  __shared__ win_t<T> dacc[DEP ? DX * DY * DZ : 1];
   __shared__ unsigned n_stray;
   int t;
   unsigned lo, hi;
@@ -422,7 +422,7 @@ __global__ void __launch_bounds__(kGatherBlock, gather_waves(WIDE, EN && HAS_Q))
     }
   }
   if constexpr (DEP)
-    for (int c = threadIdx.x; c < DX * DY * DZ; c += kGatherBlock) dacc[c] = (T)0;
+    for (int c = threadIdx.x; c < DX * DY * DZ; c += kGatherBlock) dacc[c] = (win_t<T>)0;
   __syncthreads();
   double ksum = 0.0;
   unsigned my_stray = 0;   // this thread's deposits outside the narrow window
@@ -509,7 +509,7 @@ __global__ void __launch_bounds__(kGatherBlock, gather_waves(WIDE, EN && HAS_Q))
         const int a0 = (sx * DY + sy) * DZ + sz;
 #pragma unroll
         for (int c = 0; c < 8; ++c)
-          atomicAdd(&dacc[a0 + ((c >> 2) * DY + ((c >> 1) & 1)) * DZ + (c & 1)], w[c]);
+          add_window(&dacc[a0 + ((c >> 2) * DY + ((c >> 1) & 1)) * DZ + (c & 1)], w[c]);
         if constexpr (FIXED)
           if (dfix != 0)
             atomicAdd(&dacc[a0 + ((big >> 2) * DY + ((big >> 1) & 1)) * DZ + (big & 1)],
@@ -556,7 +556,7 @@ __global__ void __launch_bounds__(kGatherBlock, gather_waves(WIDE, EN && HAS_Q))
 #pragma unroll
     for (int k = 0; k < DPER; ++k) {
       const int c = threadIdx.x + k * kGatherBlock;
-      dv[k] = (DN % kGatherBlock == 0 || c < DN) ? dacc[c] : (T)0;
+      dv[k] = (DN % kGatherBlock == 0 || c < DN) ? (T)dacc[c] : (T)0;
     }
 #pragma unroll
     for (int k = 0; k < DPER; ++k) {
