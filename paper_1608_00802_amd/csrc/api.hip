@@ -70,8 +70,8 @@ struct pm_ctx {
   unsigned* tile_counts;  // [kSlices][count_stride(tiles)]
   unsigned* scan_sums;    // [2 * scan_blocks(tiles)]
   unsigned* slice_start;  // [tiles * kSlices + 1]
-  unsigned* tile_start;   // [tiles + 1], valid once sorted
-  unsigned* chunk_start;  // [tiles + 1]
+  uint4* chunks;          // the tile map's chunk list, valid once sorted
+  unsigned* used;         // its length
   TileMap tmap;
   unsigned* sort_key;
   unsigned* sort_rank;
@@ -79,7 +79,7 @@ struct pm_ctx {
   float* vel_tmp;
   int* ids_tmp;
   int tiles;
-  bool sorted;       // tile_start describes a partition of the particles by tile
+  bool sorted;       // tmap describes a partition of the particles by tile
   int q_blocks;
   int k_blocks;
   bool have_delta;   // delta in the workspace was made by pm_deposit
@@ -138,7 +138,7 @@ int ilog2_exact(int n) {
 
 struct Layout {
   size_t mass, delta, phi, q, spec, tw, s2, partials, kpart, result, tile_counts, scan_sums,
-      slice_start, tile_start, chunk_start, sort_key, sort_rank, pos_tmp, vel_tmp, ids_tmp, total;
+      slice_start, chunks, used, sort_key, sort_rank, pos_tmp, vel_tmp, ids_tmp, total;
 };
 
 Layout layout_for(const pm_params& p) {
@@ -170,8 +170,8 @@ Layout layout_for(const pm_params& p) {
   L.tile_counts = take(4 * (size_t)kSlices * count_stride((int)tiles));
   L.scan_sums = take(8 * (size_t)scan_blocks((int)tiles));
   L.slice_start = take(4 * (tiles * kSlices + 1));
-  L.tile_start = take(4 * (tiles + 1));
-  L.chunk_start = take(4 * (tiles + 1));
+  L.chunks = take(sizeof(uint4) * (size_t)tiled_grid((int64_t)np, (int)tiles));
+  L.used = take(4);
   L.sort_key = take(4 * np);
   L.sort_rank = take(4 * np);
   L.pos_tmp = take(12 * np);
@@ -454,16 +454,16 @@ pm_status ctx_setup(pm_ctx* c, const pm_params* params, char* base, hipStream_t 
   c->tile_counts = reinterpret_cast<unsigned*>(base + L.tile_counts);
   c->scan_sums = reinterpret_cast<unsigned*>(base + L.scan_sums);
   c->slice_start = reinterpret_cast<unsigned*>(base + L.slice_start);
-  c->tile_start = reinterpret_cast<unsigned*>(base + L.tile_start);
-  c->chunk_start = reinterpret_cast<unsigned*>(base + L.chunk_start);
+  c->chunks = reinterpret_cast<uint4*>(base + L.chunks);
+  c->used = reinterpret_cast<unsigned*>(base + L.used);
   c->sort_key = reinterpret_cast<unsigned*>(base + L.sort_key);
   c->sort_rank = reinterpret_cast<unsigned*>(base + L.sort_rank);
   c->pos_tmp = reinterpret_cast<uint32_t*>(base + L.pos_tmp);
   c->vel_tmp = reinterpret_cast<float*>(base + L.vel_tmp);
   c->ids_tmp = reinterpret_cast<int*>(base + L.ids_tmp);
   c->tiles = tile_count(c->logn);
-  c->tmap.start = c->tile_start;
-  c->tmap.chunk_start = c->chunk_start;
+  c->tmap.chunks = c->chunks;
+  c->tmap.used = c->used;
   c->tmap.tiles = c->tiles;
   c->sorted = false;
   c->q_blocks = qpot_blocks(c->logn);
@@ -664,8 +664,8 @@ pm_status sort_into(pm_ctx* c, const void* pos, const float* vel, const int32_t*
                              c->sort_rank, c->stream);
   }));
   PM_TRY(timed(c, kcSortScan, [&] {
-    return launch_sort_scan(c->tile_counts, c->tiles, c->scan_sums, c->slice_start, c->tile_start,
-                            c->chunk_start, c->stream);
+    return launch_sort_scan(c->tile_counts, c->tiles, c->scan_sums, c->slice_start, c->chunks,
+                            c->used, c->stream);
   }));
   PM_TRY(timed(c, kcSortScatter, [&] {
     return launch_sort_scatter(pos, vel, ids, c->np, c->sort_key, c->sort_rank, c->slice_start,
@@ -1339,8 +1339,8 @@ pm_status pm_batch_step(pm_batch* b, void* d_pos, float* d_vel, int32_t nactive,
     PM_TRY(dev(launch_fill_zero(c->tile_counts, cbytes, c->stream, bt)));
     PM_TRY(dev(launch_sort_count(c->fixed, d_pos, c->np, c->logn, c->tile_counts, c->sort_key,
                                  c->sort_rank, c->stream, bt)));
-    PM_TRY(dev(launch_sort_scan(c->tile_counts, c->tiles, c->scan_sums, c->slice_start, c->tile_start,
-                                c->chunk_start, c->stream, bt)));
+    PM_TRY(dev(launch_sort_scan(c->tile_counts, c->tiles, c->scan_sums, c->slice_start, c->chunks,
+                                c->used, c->stream, bt)));
     PM_TRY(dev(launch_sort_scatter(d_pos, d_vel, nullptr, c->np, c->sort_key, c->sort_rank,
                                    c->slice_start, c->pos_tmp, c->vel_tmp, nullptr, c->stream,
                                    bt)));

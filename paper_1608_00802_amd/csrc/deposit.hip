@@ -113,8 +113,8 @@ __global__ void __launch_bounds__(kDepBlock) k_deposit_tiled(const void* __restr
   const int sl = bslot(bt);
   pos = poff(pos, bt, sl);
   T* mass = woff(static_cast<T*>(mass_v), bt, sl);
-  tm.start = woff(tm.start, bt, sl);
-  tm.chunk_start = woff(tm.chunk_start, bt, sl);
+  tm.chunks = woff(tm.chunks, bt, sl);
+  tm.used = woff(tm.used, bt, sl);
   int t;
   unsigned lo, hi;
   if (!chunk_of(tm, t, lo, hi)) return;

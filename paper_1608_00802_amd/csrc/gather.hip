@@ -65,61 +65,60 @@ __device__ __forceinline__ T& soa(T* base, int64_t np, int d, unsigned p) {
   return *reinterpret_cast<T*>(reinterpret_cast<B*>(base + d * np) + (p << 2));
 }
 
-// The position words and velocity of particle p.
-template <typename P>
+// The position words and (VEL) velocity of particle p.
+template <bool VEL, typename P>
 __device__ __forceinline__ void load_particle(const void* __restrict__ pos,
                                               const float* __restrict__ vel, int64_t np, P p,
                                               uint32_t raw[3], float v[3]) {
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     raw[d] = soa(static_cast<const uint32_t*>(pos), np, d, p);
-    v[d] = vel ? soa(vel, np, d, p) : 0.0f;
+    v[d] = VEL ? soa(vel, np, d, p) : 0.0f;
   }
 }
 
-// Interpolated -grad F at one particle.  at(a, b, c) returns F at offsets
+// Interpolated -2 grad F at one particle.  at(a, b, c) returns F at offsets
 // (a - 1, b - 1, c - 1) from the particle's base cell, a, b, c in 0..3.
 // Central differences at the 8 CIC nodes use the 2x2x2 core and, per axis,
 // the two planes outside it; each axis' extra nodes are consumed as soon as
-// they are read, so only the core stays live.
+// they are read, so only the core stays live.  The trilinear weights are
+// applied as nested linear interpolations (22 instructions per axis); the
+// fused multiply-adds are written out so that every kernel rounds alike.
+__device__ __forceinline__ float lerp_f(float lo, float hi, float f) {
+  return fmaf(f, hi - lo, lo);
+}
 template <typename At>
 __device__ __forceinline__ void interp_grad(const float f[3], At&& at, float g[3]) {
-  float core[2][2][2];
+  float core[2][2][2], e[2][2];
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int c = 0; c < 2; ++c) core[a][b][c] = at(1 + a, 1 + b, 1 + c);
-  const float wx[2] = {1.0f - f[0], f[0]};
-  const float wy[2] = {1.0f - f[1], f[1]};
-  const float wz[2] = {1.0f - f[2], f[2]};
-  float gx = 0.0f, gy = 0.0f, gz = 0.0f;
+  // the node at x offset 0 takes F(+1) - F(-1) = core[1] - plane -1, the one
+  // at offset 1 the plane at +2 minus core[0]; here with the opposite sign
 #pragma unroll
   for (int b = 0; b < 2; ++b)
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      // node x offset 0 -> difference F(+1) - F(-1) uses core[1] and the plane at offset -1
-      const float lo = at(0, 1 + b, 1 + c), hi = at(3, 1 + b, 1 + c);
-      gx += wy[b] * wz[c] * (wx[0] * (core[1][b][c] - lo) + wx[1] * (hi - core[0][b][c]));
-    }
+    for (int c = 0; c < 2; ++c)
+      e[b][c] = lerp_f(at(0, 1 + b, 1 + c) - core[1][b][c], core[0][b][c] - at(3, 1 + b, 1 + c),
+                       f[0]);
+  g[0] = lerp_f(lerp_f(e[0][0], e[0][1], f[2]), lerp_f(e[1][0], e[1][1], f[2]), f[1]);
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const float lo = at(1 + a, 0, 1 + c), hi = at(1 + a, 3, 1 + c);
-      gy += wx[a] * wz[c] * (wy[0] * (core[a][1][c] - lo) + wy[1] * (hi - core[a][0][c]));
-    }
+    for (int c = 0; c < 2; ++c)
+      e[a][c] = lerp_f(at(1 + a, 0, 1 + c) - core[a][1][c], core[a][0][c] - at(1 + a, 3, 1 + c),
+                       f[1]);
+  g[1] = lerp_f(lerp_f(e[0][0], e[0][1], f[2]), lerp_f(e[1][0], e[1][1], f[2]), f[0]);
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const float lo = at(1 + a, 1 + b, 0), hi = at(1 + a, 1 + b, 3);
-      gz += wx[a] * wy[b] * (wz[0] * (core[a][b][1] - lo) + wz[1] * (hi - core[a][b][0]));
-    }
-  g[0] = -0.5f * gx;
-  g[1] = -0.5f * gy;
-  g[2] = -0.5f * gz;
+    for (int b = 0; b < 2; ++b)
+      e[a][b] = lerp_f(at(1 + a, 1 + b, 0) - core[a][b][1], core[a][b][0] - at(1 + a, 1 + b, 3),
+                       f[2]);
+  g[2] = lerp_f(lerp_f(e[0][0], e[0][1], f[1]), lerp_f(e[1][0], e[1][1], f[1]), f[0]);
 }
 
 // Low 32 bits of rint(a * b), ties to even: the drift in fixed-point units,
@@ -182,13 +181,13 @@ __device__ __forceinline__ float mesh_f(const float* __restrict__ phi, const flo
   return phi[idx];
 }
 
-// The factor on the interpolated gradient (fg without Q, see mesh_f).
+// interp_grad gives twice the gradient: the factor on it is one half, times
+// fg without Q (see mesh_f).
 template <bool HAS_Q>
 __device__ __forceinline__ void scale_grad(const GatherConst& gc, float g[3]) {
-  if constexpr (!HAS_Q) {
+  const float k = HAS_Q ? 0.5f : 0.5f * gc.fg;
 #pragma unroll
-    for (int d = 0; d < 3; ++d) g[d] *= gc.fg;
-  }
+  for (int d = 0; d < 3; ++d) g[d] *= k;
 }
 
 // mesh_f at a byte offset below 2^32 (the mesh is at most 512^3 floats).
@@ -235,8 +234,9 @@ __device__ __forceinline__ void split_kick(const GatherConst& gc, const float vi
                                            float g[3], double& ksum) {
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    vk[d] = vin[d] + fmaf(gc.fq, gq[d], gc.fg * gp[d]);
-    g[d] = fmaf(gc.oq, gq[d], gc.og * gp[d]);
+    const float hp = 0.5f * gp[d], hq = 0.5f * gq[d];
+    vk[d] = vin[d] + fmaf(gc.fq, hq, gc.fg * hp);
+    g[d] = fmaf(gc.oq, hq, gc.og * hp);
     ksum += (double)vk[d] * (double)vk[d];
   }
 }
@@ -274,7 +274,7 @@ __global__ void __launch_bounds__(kBlock) k_gather(void* __restrict__ pos,
     int ic[3];
     float f[3], xf[3], vin[3];
     uint32_t u[3], raw[3];
-    load_particle(pos, MODE == kForce ? nullptr : vel, np, p, raw, vin);
+    load_particle<MODE != kForce>(pos, vel, np, p, raw, vin);
     decode_cell<LOGN, FIXED>(raw, ic, f, u, xf);
     auto node = [&](int a, int b, int c) {
       return ((size_t)((ic[0] + a - 1) & MASK) * N + ((ic[1] + b - 1) & MASK)) * N +
@@ -312,26 +312,78 @@ __global__ void __launch_bounds__(kBlock) k_gather(void* __restrict__ pos,
   }
 }
 
-// Tiled gather: block b owns tile b of the particle sort.  F = fg phi + fq Q
-// is staged once for the tile's window (cells -1 .. T+1 around the tile) in
-// LDS; particles still inside their tile read their 32 nodes from LDS,
-// particles that left it read the mesh directly.
-// WIDE: a one-cell larger gather window and a two-cell deposit halo, for
-// steps whose particles have moved since the sort in a clustered state.
-// Waves per SIMD that the LDS windows leave room for (three 512-thread
-// blocks per CU with the narrow windows, two with the wide ones or two
-// energy-form windows); the register budget is held to that.
-constexpr int gather_waves(int wide, bool two_windows) { return wide || two_windows ? 4 : 6; }
+// Rows of an LDS window of WX x WY rows of TZ + BEFORE + AFTER cells around a
+// tile at (ox, oy, oz) (the window's first cell is at (x0, y0, oz - BEFORE)):
+// fn(k, row, z, cell) for this thread's k-th cell, z its place in the row and
+// cell its mesh index.  The tile's own TZ cells of a row, whole aligned lines
+// of the mesh, go to TZ consecutive lanes; the rows' ends follow.
+template <int LOGN, int WX, int WY, int BEFORE, int AFTER>
+struct Window {
+  static constexpr int N = 1 << LOGN, MASK = N - 1, TZ = 1 << tile_lz(LOGN);
+  static constexpr int WZ = TZ + BEFORE + AFTER, ROWS = WX * WY, SIZE = ROWS * WZ;
+  static constexpr int STEP = kGatherBlock / TZ;             // rows per pass
+  static constexpr int PC = (ROWS + STEP - 1) / STEP;        // passes over the rows' cores
+  static constexpr int ENDS = ROWS * (BEFORE + AFTER);
+  static constexpr int PE = (ENDS + kGatherBlock - 1) / kGatherBlock;
+  static constexpr int PER = PC + PE;
+  template <class F>
+  static __device__ __forceinline__ void each(int x0, int y0, int oz, F&& fn) {
+    auto row_cell = [&](int row) {
+      const int lx = row / WY, ly = row % WY;
+      return ((((x0 + lx) & MASK) << LOGN) + ((y0 + ly) & MASK)) << LOGN;
+    };
+    const int z = threadIdx.x % TZ;
+#pragma unroll
+    for (int k = 0; k < PC; ++k) {
+      const int row = threadIdx.x / TZ + k * STEP;
+      if (row < ROWS) fn(k, row, z + BEFORE, row_cell(row) + oz + z);
+    }
+#pragma unroll
+    for (int k = 0; k < PE; ++k) {
+      const int e = threadIdx.x + k * kGatherBlock;
+      if (e < ENDS) {
+        const int row = e / (BEFORE + AFTER), j = e % (BEFORE + AFTER);
+        const int lz = j < BEFORE ? j : j + TZ;
+        fn(PC + k, row, lz, row_cell(row) + ((oz - BEFORE + lz) & MASK));
+      }
+    }
+  }
+};
+
+// Tiled gather: a block takes one chunk of the particle sort, in two phases
+// that use the same LDS one after the other.
+//   1. F = fg phi + fq Q (or psi) of the tile's window is staged in LDS;
+//      every particle reads its 32 nodes there, is kicked and drifted, and
+//      goes back to memory.
+//   2. DEP: the window is cleared and becomes the deposit's accumulator; the
+//      particles' new positions are read back (12 bytes each, from L2) and
+//      their CIC weights added; the window is then added to the mass mesh.
+// With both windows in LDS at once (51 KB without a gather halo, three blocks
+// per CU) a particle that had left its tile read its 32 nodes from the mesh,
+// and one such lane holds its wave.  In turn they fit 34 KB, four blocks per
+// CU, with a gather window that is wider by HG cells on each side: 302 -> 269
+// us per launch over the 24 steps after a sort of a 256^3 field (1 cell rms
+// from the lattice, 0.02 cells per step), 354 -> 321 us on clumps over an
+// empty background, and 321 -> 208 us for the closing half-kick.  What bounds
+// it: phase 1 alone takes 192 us, 4.5 TB/s of particle traffic where a copy
+// reaches 5.1; the window flush, one u64 atomic per non-zero cell (2.07 per
+// mesh cell), 53 us; the weights and LDS adds 24 us.
+// WIDE: one cell more of halo in both windows, for steps whose particles have
+// moved since the sort in a clustered state.
+#ifndef FDM_GATHER_WAVES
+#define FDM_GATHER_WAVES 8
+#endif
+// Waves per SIMD that the LDS windows leave room for; the register budget is
+// held to that.
+constexpr int gather_waves(int wide, bool two_windows) {
+  return wide ? 6 : two_windows ? 6 : FDM_GATHER_WAVES;
+}
 
 template <int LOGN, bool FIXED, bool HAS_Q, int MODE, bool DEP, int WIDE = 0, bool EN = false>
 __global__ void __launch_bounds__(kGatherBlock, gather_waves(WIDE, EN && HAS_Q))
-    k_gather_tiled(void* __restrict__ pos,
-                                                         float* __restrict__ vel,
-                                                         const float* __restrict__ phi,
-                                                         const float* __restrict__ q, int64_t np,
-                                                         TileMap tm, GatherConst gc,
-                                                         float* __restrict__ acc,
-                                                         void* __restrict__ mass_v, Batch bt) {
+    k_gather_tiled(void* __restrict__ pos, float* __restrict__ vel, const float* __restrict__ phi,
+                   const float* __restrict__ q, int64_t np, TileMap tm, GatherConst gc,
+                   float* __restrict__ acc, void* __restrict__ mass_v, Batch bt) {
   {
     const int sl = bslot(bt);
     pos = poff(pos, bt, sl);
@@ -340,8 +392,8 @@ __global__ void __launch_bounds__(kGatherBlock, gather_waves(WIDE, EN && HAS_Q))
     phi = woff(phi, bt, sl);
     q = woff(q, bt, sl);
     mass_v = woff(mass_v, bt, sl);
-    tm.start = woff(tm.start, bt, sl);
-    tm.chunk_start = woff(tm.chunk_start, bt, sl);
+    tm.chunks = woff(tm.chunks, bt, sl);
+    tm.used = woff(tm.used, bt, sl);
     if (bt.consts) {
       const SlotConst& sc = bt.consts[blockIdx.y];
       if (!gc.psi) {
@@ -352,19 +404,22 @@ __global__ void __launch_bounds__(kGatherBlock, gather_waves(WIDE, EN && HAS_Q))
     }
   }
   using T = typename std::conditional<FIXED, unsigned long long, float>::type;
+  using A = win_t<T>;
   constexpr int N = 1 << LOGN;
   constexpr int MASK = N - 1;
   constexpr int TX = 1 << tile_lx(LOGN), TY = 1 << tile_ly(LOGN), TZ = 1 << tile_lz(LOGN);
-  constexpr int HG = WIDE ? 1 : kGatherHalo, HD = WIDE ? 2 : kDepHalo;
-  // F window: cells o - 1 - HG .. o + T + 1 + HG; deposit window: o - HD .. o + T + HD
-  constexpr int WX = TX + 3 + 2 * HG, WY = TY + 3 + 2 * HG, WZ = TZ + 3 + 2 * HG;
   constexpr int NTY = N / TY, NTZ = N / TZ;
-  constexpr int DX = TX + 1 + 2 * HD, DY = TY + 1 + 2 * HD, DZ = TZ + 1 + 2 * HD;
-  __shared__ float win[WX * WY * WZ];
-  // energy form: win holds phi and winq holds Q (interpolated separately)
-  __shared__ float winq[EN && HAS_Q ? WX * WY * WZ : 1];
-  __shared__ win_t<T> dacc[DEP ? DX * DY * DZ : 1];
-  __shared__ unsigned n_stray;
+  constexpr int HG = kGatherHalo + WIDE, HD = kDepHalo + WIDE;
+  // F window: cells o - 1 - HG .. o + T + 1 + HG; deposit window: o - HD .. o + T + HD
+  using FW = Window<LOGN, TX + 3 + 2 * HG, TY + 3 + 2 * HG, 1 + HG, 2 + HG>;
+  using DW = Window<LOGN, TX + 1 + 2 * HD, TY + 1 + 2 * HD, HD, 1 + HD>;
+  constexpr int WY = TY + 3 + 2 * HG, WZ = FW::WZ, DY = TY + 1 + 2 * HD, DZ = DW::WZ;
+  constexpr bool TWO = EN && HAS_Q;   // win holds phi and winq Q, interpolated separately
+  constexpr size_t kF = sizeof(float) * FW::SIZE * (TWO ? 2 : 1);
+  constexpr size_t kD = DEP ? (sizeof(A) * DW::SIZE + 15) & ~(size_t)15 : 0;
+  __shared__ __align__(16) unsigned char lds[kF > kD ? kF : kD];
+  float* win = reinterpret_cast<float*>(lds);
+  float* winq = win + (TWO ? FW::SIZE : 0);
   int t;
   unsigned lo, hi;
   if (!chunk_of(tm, t, lo, hi)) {
@@ -372,85 +427,48 @@ __global__ void __launch_bounds__(kGatherBlock, gather_waves(WIDE, EN && HAS_Q))
       if (threadIdx.x == 0) gc.kpart[blockIdx.x] = 0.0;
     return;
   }
-  if (threadIdx.x == 0) n_stray = 0;
   // the first particles' loads are in flight while the window is staged;
-  // afterwards particle p + PF * kGatherBlock is loaded while p is processed
-  constexpr int PF = kGatherPrefetch;
-  uint32_t raw_n[PF][3];
-  float vin_n[PF][3];
-#pragma unroll
-  for (int k = 0; k < PF; ++k) {
-    const unsigned pk = lo + threadIdx.x + k * kGatherBlock;
-    if (pk < hi) load_particle(pos, vel, np, pk, raw_n[k], vin_n[k]);
-  }
+  // afterwards particle p + kGatherBlock is loaded while p is processed
+  uint32_t raw_n[3];
+  float vin_n[3];
+  unsigned p = lo + threadIdx.x;
+  if (p < hi) load_particle<true>(pos, vel, np, p, raw_n, vin_n);
   const int ox = (t / (NTY * NTZ)) * TX, oy = ((t / NTZ) % NTY) * TY, oz = (t % NTZ) * TZ;
-  if constexpr (EN) {
-    for (int c = threadIdx.x; c < WX * WY * WZ; c += kGatherBlock) {
-      const int lx = c / (WY * WZ), ly = (c / WZ) % WY, lz = c % WZ;
-      const size_t idx = ((size_t)((ox - 1 - HG + lx) & MASK) * N +
-                          ((oy - 1 - HG + ly) & MASK)) * N + ((oz - 1 - HG + lz) & MASK);
-      win[c] = phi[idx];
-      if constexpr (HAS_Q) winq[c] = q[idx];
-    }
-  } else if constexpr (HAS_Q) {
-    for (int c = threadIdx.x; c < WX * WY * WZ; c += kGatherBlock) {
-      const int lx = c / (WY * WZ), ly = (c / WZ) % WY, lz = c % WZ;
-      const size_t idx = ((size_t)((ox - 1 - HG + lx) & MASK) * N +
-                          ((oy - 1 - HG + ly) & MASK)) * N + ((oz - 1 - HG + lz) & MASK);
-      win[c] = mesh_f<LOGN, HAS_Q>(phi, q, gc, idx);
-    }
-  } else {
+  {
     // all of a thread's window loads are issued before the first is used
-    // (faster for the one-field window; the two-field one was slower so)
-    constexpr int WN = WX * WY * WZ;
-    constexpr int WPER = (WN + kGatherBlock - 1) / kGatherBlock;
-    float wphi[WPER];
-#pragma unroll
-    for (int k = 0; k < WPER; ++k) {
-      const int c = threadIdx.x + k * kGatherBlock;
-      if (WN % kGatherBlock == 0 || c < WN) {
-        const int lx = c / (WY * WZ), ly = (c / WZ) % WY, lz = c % WZ;
-        const size_t idx = ((size_t)((ox - 1 - HG + lx) & MASK) * N +
-                            ((oy - 1 - HG + ly) & MASK)) * N + ((oz - 1 - HG + lz) & MASK);
-        wphi[k] = phi[idx];
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < WPER; ++k) {
-      const int c = threadIdx.x + k * kGatherBlock;
-      if (WN % kGatherBlock == 0 || c < WN) win[c] = wphi[k];   // mesh_f without Q
-    }
+    float w[FW::PER], wq[HAS_Q ? FW::PER : 1];
+    const int x0 = ox - 1 - HG, y0 = oy - 1 - HG;
+    FW::each(x0, y0, oz, [&](int k, int, int, int cell) {
+      w[k] = phi[cell];
+      if constexpr (HAS_Q) wq[k] = q[cell];
+    });
+    FW::each(x0, y0, oz, [&](int k, int row, int z, int) {
+      if constexpr (HAS_Q && !EN)
+        win[row * WZ + z] = fmaf(gc.fq, wq[k], gc.fg * w[k]);   // as mesh_f
+      else
+        win[row * WZ + z] = w[k];
+      if constexpr (TWO) winq[row * WZ + z] = wq[k];
+    });
   }
-  if constexpr (DEP)
-    for (int c = threadIdx.x; c < DX * DY * DZ; c += kGatherBlock) dacc[c] = (win_t<T>)0;
   __syncthreads();
   double ksum = 0.0;
-  unsigned my_stray = 0;   // this thread's deposits outside the narrow window
-  for (unsigned p = lo + threadIdx.x; p < hi; p += kGatherBlock) {
+  for (; p < hi; p += kGatherBlock) {
     int ic[3];
     float f[3], xf[3], vin[3];
     uint32_t u[3], raw[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-      raw[d] = raw_n[0][d];
-      vin[d] = vin_n[0][d];
+      raw[d] = raw_n[d];
+      vin[d] = vin_n[d];
     }
-#pragma unroll
-    for (int k = 0; k + 1 < PF; ++k)
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        raw_n[k][d] = raw_n[k + 1][d];
-        vin_n[k][d] = vin_n[k + 1][d];
-      }
-    if (p + PF * kGatherBlock < hi)
-      load_particle(pos, vel, np, p + PF * kGatherBlock, raw_n[PF - 1], vin_n[PF - 1]);
+    if (p + kGatherBlock < hi) load_particle<true>(pos, vel, np, p + kGatherBlock, raw_n, vin_n);
     decode_cell<LOGN, FIXED>(raw, ic, f, u, xf);
     const int rx = (ic[0] - ox + HG) & MASK, ry = (ic[1] - oy + HG) & MASK,
               rz = (ic[2] - oz + HG) & MASK;
     const bool in_win = rx < TX + 2 * HG && ry < TY + 2 * HG && rz < TZ + 2 * HG;
     // one base index; the 32 nodes at constant offsets from it
     const int lbase = (rx * WY + ry) * WZ + rz;
-    auto lds = [&](int a, int b, int c) { return lbase + (a * WY + b) * WZ + c; };
+    auto lds_at = [&](int a, int b, int c) { return lbase + (a * WY + b) * WZ + c; };
     auto node = [&](int a, int b, int c) {
       return ((size_t)((ic[0] + a - 1) & MASK) * N + ((ic[1] + b - 1) & MASK)) * N +
              ((ic[2] + c - 1) & MASK);
@@ -459,9 +477,9 @@ __global__ void __launch_bounds__(kGatherBlock, gather_waves(WIDE, EN && HAS_Q))
     if constexpr (EN) {
       float gp[3], gq[3] = {0.0f, 0.0f, 0.0f};
       if (in_win) {
-        interp_grad(f, [&](int a, int b, int c) { return win[lds(a, b, c)]; }, gp);
+        interp_grad(f, [&](int a, int b, int c) { return win[lds_at(a, b, c)]; }, gp);
         if constexpr (HAS_Q)
-          interp_grad(f, [&](int a, int b, int c) { return winq[lds(a, b, c)]; }, gq);
+          interp_grad(f, [&](int a, int b, int c) { return winq[lds_at(a, b, c)]; }, gq);
       } else {
         interp_grad(f, [&](int a, int b, int c) { return phi[node(a, b, c)]; }, gp);
         if constexpr (HAS_Q)
@@ -470,7 +488,7 @@ __global__ void __launch_bounds__(kGatherBlock, gather_waves(WIDE, EN && HAS_Q))
       split_kick(gc, vin, gp, gq, vk, g, ksum);
     } else {
       if (in_win) {
-        interp_grad(f, [&](int a, int b, int c) { return win[lds(a, b, c)]; }, g);
+        interp_grad(f, [&](int a, int b, int c) { return win[lds_at(a, b, c)]; }, g);
       } else {
         // byte offsets of the 4 x 4 x 4 neighbourhood from per-axis terms
         // (disjoint bit fields: one or per node)
@@ -492,16 +510,38 @@ __global__ void __launch_bounds__(kGatherBlock, gather_waves(WIDE, EN && HAS_Q))
     uint32_t unew[3];
     float xnew[3];
     push<LOGN, FIXED, MODE>(pos, vel, acc, np, p, g, vk, u, xf, gc.fd_units, unew, xnew, mass_v);
-    if constexpr (DEP) {
+  }
+  if constexpr (EN) {
+    __shared__ double kred[kGatherBlock / 64];
+    const double kt = block_total<kGatherBlock>(ksum, kred);
+    if (threadIdx.x == 0) gc.kpart[blockIdx.x] = kt;
+  }
+  if constexpr (DEP) {
+    A* dacc = reinterpret_cast<A*>(lds);
+    __syncthreads();   // the last reads of F
+    for (int c = threadIdx.x; c < (int)(kD / 16); c += kGatherBlock)
+      reinterpret_cast<uint4*>(lds)[c] = make_uint4(0u, 0u, 0u, 0u);
+    p = lo + threadIdx.x;
+    if (p < hi) load_particle<false>(pos, vel, np, p, raw_n, vin_n);
+    __syncthreads();
+    T* mass = static_cast<T*>(mass_v);
+    unsigned my_stray = 0;   // this thread's deposits outside the narrow window
+    for (; p < hi; p += kGatherBlock) {
+      uint32_t raw[3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) raw[d] = raw_n[d];
+      if (p + kGatherBlock < hi)
+        load_particle<false>(pos, vel, np, p + kGatherBlock, raw_n, vin_n);
       // natural corner order (consecutive lanes of a wave add to neighbouring
       // cells together); the fixed-point remainder d goes to the heaviest
       // corner in a ninth add where it is not zero
       int jx, jy, jz, big = 0, dfix = 0;
       T w[8];
       if constexpr (FIXED)
-        fixed_weights_split<LOGN>(unew[0], unew[1], unew[2], jx, jy, jz, w, big, dfix);
+        fixed_weights_split<LOGN>(raw[0], raw[1], raw[2], jx, jy, jz, w, big, dfix);
       else
-        float_weights<LOGN>(xnew[0], xnew[1], xnew[2], jx, jy, jz, w);
+        float_weights<LOGN>(__uint_as_float(raw[0]), __uint_as_float(raw[1]),
+                            __uint_as_float(raw[2]), jx, jy, jz, w);
       const int sx = (jx - ox + HD) & MASK, sy = (jy - oy + HD) & MASK,
                 sz = (jz - oz + HD) & MASK;
       const bool inside = sx < TX + 2 * HD && sy < TY + 2 * HD && sz < TZ + 2 * HD;
@@ -512,62 +552,40 @@ __global__ void __launch_bounds__(kGatherBlock, gather_waves(WIDE, EN && HAS_Q))
           add_window(&dacc[a0 + ((c >> 2) * DY + ((c >> 1) & 1)) * DZ + (c & 1)], w[c]);
         if constexpr (FIXED)
           if (dfix != 0)
-            atomicAdd(&dacc[a0 + ((big >> 2) * DY + ((big >> 1) & 1)) * DZ + (big & 1)],
-                      (T)(long long)dfix);
+            add_window(&dacc[a0 + ((big >> 2) * DY + ((big >> 1) & 1)) * DZ + (big & 1)],
+                       (T)(long long)dfix);
       } else {
         if constexpr (FIXED) {
 #pragma unroll
           for (int c = 0; c < 8; ++c)
             if (c == big) w[c] += (T)(long long)dfix;
         }
-        deposit_global<LOGN>(static_cast<T*>(mass_v), jx, jy, jz, w);
+        deposit_global<LOGN>(mass, jx, jy, jz, w);
       }
       // count strays (always against the narrow deposit window, so that the
       // sort interval chosen from them does not depend on the window used)
       constexpr int HN = kDepHalo;
-      const bool inside_n = ((jx - ox + HN) & MASK) < TX + 2 * HN &&
-                            ((jy - oy + HN) & MASK) < TY + 2 * HN &&
-                            ((jz - oz + HN) & MASK) < TZ + 2 * HN;
+      const bool inside_n = HD == HN ? inside
+                                     : ((jx - ox + HN) & MASK) < TX + 2 * HN &&
+                                           ((jy - oy + HN) & MASK) < TY + 2 * HN &&
+                                           ((jz - oz + HN) & MASK) < TZ + 2 * HN;
       my_stray += inside_n ? 0u : 1u;
     }
-  }
-  if constexpr (DEP) {
-    // one LDS add per wave
     for (int off = 32; off > 0; off >>= 1) my_stray += __shfl_down(my_stray, off, 64);
-    if ((threadIdx.x & 63) == 0 && my_stray) atomicAdd(&n_stray, my_stray);
-  }
-  if constexpr (EN) {
-    __shared__ double kred[kGatherBlock / 64];
-    const double kt = block_total<kGatherBlock>(ksum, kred);
-    if (threadIdx.x == 0) gc.kpart[blockIdx.x] = kt;
-  }
-  if constexpr (DEP) {
-    __syncthreads();
-    T* mass = static_cast<T*>(mass_v);
-    if (threadIdx.x == 0 && n_stray)
+    if ((threadIdx.x & 63) == 0 && my_stray)
       atomicAdd(reinterpret_cast<unsigned*>(reinterpret_cast<char*>(mass_v) +
                                             8 * ((size_t)N * N * N)) +
                     (blockIdx.x % kStraySlices) * kStrayStride,
-                n_stray);
+                my_stray);
+    __syncthreads();
     // all of a thread's window cells are read before the first atomic
-    constexpr int DN = DX * DY * DZ;
-    constexpr int DPER = (DN + kGatherBlock - 1) / kGatherBlock;
-    T dv[DPER];
-#pragma unroll
-    for (int k = 0; k < DPER; ++k) {
-      const int c = threadIdx.x + k * kGatherBlock;
-      dv[k] = (DN % kGatherBlock == 0 || c < DN) ? (T)dacc[c] : (T)0;
-    }
-#pragma unroll
-    for (int k = 0; k < DPER; ++k) {
-      const int c = threadIdx.x + k * kGatherBlock;
-      if (dv[k] != (T)0) {
-        const int lx = c / (DY * DZ), ly = (c / DZ) % DY, lz = c % DZ;
-        const size_t cell = ((size_t)((ox - HD + lx) & MASK) * N + ((oy - HD + ly) & MASK)) * N +
-                            ((oz - HD + lz) & MASK);
-        add_global(&mass[cell], dv[k]);
-      }
-    }
+    T dv[DW::PER];
+    DW::each(ox - HD, oy - HD, oz, [&](int k, int row, int z, int) {
+      dv[k] = (T)dacc[row * DZ + z];
+    });
+    DW::each(ox - HD, oy - HD, oz, [&](int k, int, int, int cell) {
+      if (dv[k] != (T)0) add_global(&mass[cell], dv[k]);
+    });
   }
 }
 

@@ -27,12 +27,6 @@ constexpr int kBlock = 256;               // threads per block of the streaming 
 #define FDM_GATHER_BLOCK 512
 #endif
 constexpr int kGatherBlock = FDM_GATHER_BLOCK;  // threads per block of the tiled gather
-#ifndef FDM_GATHER_PREFETCH
-#define FDM_GATHER_PREFETCH 1
-#endif
-// Particles whose loads a tiled-gather thread keeps in flight ahead of the
-// one it processes.
-constexpr int kGatherPrefetch = FDM_GATHER_PREFETCH;
 constexpr int kMassShift = 40;            // one particle = 2^40 integer mass units
 
 // Particle tiles of the sort, the tiled deposit and the tiled gather:
@@ -52,7 +46,7 @@ constexpr int kTileLX = FDM_TILE_LX, kTileLY = FDM_TILE_LY, kTileLZ = FDM_TILE_L
 // out of their tile is still in LDS) and of the tiled deposit (the same for
 // deposits that land up to kDepHalo cells out of the tile).
 #ifndef FDM_GATHER_HALO
-#define FDM_GATHER_HALO 0
+#define FDM_GATHER_HALO 1
 #endif
 #ifndef FDM_DEP_HALO
 #define FDM_DEP_HALO 1
@@ -204,46 +198,31 @@ hipError_t launch_deposit_fixed(const uint32_t* pos, int64_t np, int logn,
                                 const Batch& bt = Batch());
 hipError_t launch_deposit_f32(const float* pos, int64_t np, int logn, float* acc,
                               hipStream_t s, const Batch& bt = Batch());
-// Tiled variants.  The particle sort leaves tile ranges and their chunking:
+// Tiled variants.  The particle sort leaves the list of chunks: chunk k holds
+// the particles [y, z) of tile x (at most kChunk of them), *used chunks in all.
 struct TileMap {
-  const unsigned* start;        // [tiles + 1] first particle of each tile
-  const unsigned* chunk_start;  // [tiles + 1] first chunk of each tile
+  const uint4* chunks;
+  const unsigned* used;
   int tiles;
 };
 // upper bound of the number of chunks: every chunk is full except one per tile
 inline unsigned tiled_grid(int64_t np, int tiles) {
   return (unsigned)(tiles + (np + kChunk - 1) / kChunk);
 }
-// Block b of a tiled launch handles chunk b: tile t with chunk_start[t] <= b <
-// chunk_start[t + 1] and particles [start[t] + j kChunk, ...) of it,
-// j = b - chunk_start[t].  Returns false for blocks beyond the last chunk
-// (the same answer for every thread of the block).
+// The chunk of this block of a tiled launch: its tile and particles [lo, hi);
+// false for blocks beyond the last chunk (the same answer for every thread of
+// the block).  Two dependent loads: looking the tile up in the tiles' chunk
+// offsets by bisection cost a chain of 13 at 256^3 (8192 tiles), which no
+// load of the block could overtake.
 __device__ __forceinline__ bool chunk_of(const TileMap& tm, int& tile, unsigned& lo,
                                          unsigned& hi) {
-  __shared__ int s_tile;
-  __shared__ unsigned s_chunk;
-  if (threadIdx.x == 0) {
-    const unsigned used = tm.chunk_start[tm.tiles];
-    const unsigned b = xcd_block(blockIdx.x, used, xcd_group(FDM_XCD_TILES, used));
-    int t = -1;
-    if (b < used) {
-      int l = 0, r = tm.tiles;  // first index with chunk_start > b lies in (l, r]
-      while (r - l > 1) {
-        const int m = (l + r) >> 1;
-        if (tm.chunk_start[m] <= b) l = m; else r = m;
-      }
-      t = l;
-    }
-    s_tile = t;
-    s_chunk = b;
-  }
-  __syncthreads();
-  tile = s_tile;
-  if (tile < 0) return false;
-  const unsigned j = s_chunk - tm.chunk_start[tile];
-  lo = tm.start[tile] + j * (unsigned)kChunk;
-  const unsigned end = tm.start[tile + 1];
-  hi = lo + (unsigned)kChunk < end ? lo + (unsigned)kChunk : end;
+  const unsigned used = __builtin_amdgcn_readfirstlane(*tm.used);
+  const unsigned b = xcd_block(blockIdx.x, used, xcd_group(FDM_XCD_TILES, used));
+  if (b >= used) return false;
+  const uint4 c = tm.chunks[b];
+  tile = (int)__builtin_amdgcn_readfirstlane(c.x);
+  lo = __builtin_amdgcn_readfirstlane(c.y);
+  hi = __builtin_amdgcn_readfirstlane(c.z);
   return true;
 }
 
@@ -258,10 +237,10 @@ hipError_t launch_deposit_f32_tiled(const float* pos, int64_t np, int logn, cons
 hipError_t launch_sort_count(bool fixed, const void* pos, int64_t np, int logn,
                              unsigned* counts, unsigned* key, unsigned* rank, hipStream_t s,
                              const Batch& bt = Batch());
-// slice_start: [tiles * kSlices + 1]; tile_start, chunk_start: [tiles + 1];
+// slice_start: [tiles * kSlices + 1]; chunks, used: the TileMap's lists;
 // sums: scratch of 2 * scan_blocks(tiles) counters
 hipError_t launch_sort_scan(const unsigned* counts, int tiles, unsigned* sums,
-                            unsigned* slice_start, unsigned* tile_start, unsigned* chunk_start,
+                            unsigned* slice_start, uint4* chunks, unsigned* used,
                             hipStream_t s, const Batch& bt = Batch());
 hipError_t launch_sort_scatter(const void* pos, const float* vel, const int* ids, int64_t np,
                                const unsigned* key, const unsigned* rank,

@@ -204,21 +204,22 @@ __global__ void __launch_bounds__(kScanBlock) k_sort_scan_reduce(const unsigned*
   }
 }
 
-// Down-sweep: offsets of the earlier blocks, then per-tile prefix sums.
+// Down-sweep: offsets of the earlier blocks, then per-tile prefix sums and
+// the tile's entries of the chunk list.
 __global__ void __launch_bounds__(kScanBlock) k_sort_scan_down(const unsigned* __restrict__ counts,
                                                               int tiles, int cstride,
                                                               const unsigned* __restrict__ sums,
                                                               unsigned* __restrict__ slice_start,
-                                                              unsigned* __restrict__ tile_start,
-                                                              unsigned* __restrict__ chunk_start,
+                                                              uint4* __restrict__ chunks,
+                                                              unsigned* __restrict__ used,
                                                               Batch bt) {
   {
     const int sl = bslot(bt);
     counts = woff(counts, bt, sl);
     sums = woff(sums, bt, sl);
     slice_start = woff(slice_start, bt, sl);
-    tile_start = woff(tile_start, bt, sl);
-    chunk_start = woff(chunk_start, bt, sl);
+    chunks = woff(chunks, bt, sl);
+    used = woff(used, bt, sl);
   }
   __shared__ unsigned off[2];
   if (threadIdx.x < 64) {
@@ -250,8 +251,11 @@ __global__ void __launch_bounds__(kScanBlock) k_sort_scan_down(const unsigned* _
   a += off[0];
   b += off[1];
   if (t < tiles) {
-    tile_start[t] = a;
-    chunk_start[t] = b;
+    unsigned tot = 0;
+#pragma unroll
+    for (int s = 0; s < kSlices; ++s) tot += c[s];
+    for (unsigned p = a; p < a + tot; p += kChunk)
+      chunks[b++] = make_uint4((unsigned)t, p, min(p + (unsigned)kChunk, a + tot), 0u);
     unsigned r = a;
     uint4* s4 = reinterpret_cast<uint4*>(slice_start + (size_t)t * kSlices);
 #pragma unroll
@@ -267,8 +271,7 @@ __global__ void __launch_bounds__(kScanBlock) k_sort_scan_down(const unsigned* _
   }
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
     slice_start[(size_t)tiles * kSlices] = off[0] + ta;
-    tile_start[tiles] = off[0] + ta;
-    chunk_start[tiles] = off[1] + tb;
+    *used = off[1] + tb;
   }
 }
 
@@ -323,13 +326,13 @@ hipError_t launch_sort_count(bool fixed, const void* pos, int64_t np, int logn,
 }
 
 hipError_t launch_sort_scan(const unsigned* counts, int tiles, unsigned* sums,
-                            unsigned* slice_start, unsigned* tile_start, unsigned* chunk_start,
+                            unsigned* slice_start, uint4* chunks, unsigned* used,
                             hipStream_t s, const Batch& bt) {
   const dim3 g(scan_blocks(tiles), bt.count);
   const int cs = count_stride(tiles);
   hipLaunchKernelGGL(k_sort_scan_reduce, g, dim3(kScanBlock), 0, s, counts, tiles, cs, sums, bt);
   hipLaunchKernelGGL(k_sort_scan_down, g, dim3(kScanBlock), 0, s, counts, tiles, cs, sums,
-                     slice_start, tile_start, chunk_start, bt);
+                     slice_start, chunks, used, bt);
   return hipGetLastError();
 }
 
