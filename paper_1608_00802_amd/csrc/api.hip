@@ -68,10 +68,11 @@ struct pm_ctx {
   double* kpart;     // |p|^2 partial sums of the energy form of the gather
   double* result;    // reduced energies (device)
   unsigned* tile_counts;  // [kSlices][count_stride(tiles)]
-  unsigned* scan_sums;    // [2 * scan_blocks(tiles)]
+  unsigned* scan_sums;    // [3 * scan_blocks(tiles)]
   unsigned* slice_start;  // [tiles * kSlices + 1]
-  uint4* chunks;          // the tile map's chunk list, valid once sorted
-  unsigned* used;         // its length
+  uint4* chunks;          // the tile map's chunk and piece lists, valid once sorted
+  uint4* pieces;
+  unsigned* used;         // their lengths
   TileMap tmap;
   unsigned* sort_key;
   unsigned* sort_rank;
@@ -138,7 +139,7 @@ int ilog2_exact(int n) {
 
 struct Layout {
   size_t mass, delta, phi, q, spec, tw, s2, partials, kpart, result, tile_counts, scan_sums,
-      slice_start, chunks, used, sort_key, sort_rank, pos_tmp, vel_tmp, ids_tmp, total;
+      slice_start, chunks, pieces, used, sort_key, sort_rank, pos_tmp, vel_tmp, ids_tmp, total;
 };
 
 Layout layout_for(const pm_params& p) {
@@ -168,10 +169,11 @@ Layout layout_for(const pm_params& p) {
   L.kpart = take(8 * std::max<size_t>(65536, tiles + (np + kChunk - 1) / kChunk));
   L.result = take(8 * 16);
   L.tile_counts = take(4 * (size_t)kSlices * count_stride((int)tiles));
-  L.scan_sums = take(8 * (size_t)scan_blocks((int)tiles));
+  L.scan_sums = take(12 * (size_t)scan_blocks((int)tiles));
   L.slice_start = take(4 * (tiles * kSlices + 1));
   L.chunks = take(sizeof(uint4) * (size_t)tiled_grid((int64_t)np, (int)tiles));
-  L.used = take(4);
+  L.pieces = take(sizeof(uint4) * (size_t)piece_bound((int64_t)np, (int)tiles));
+  L.used = take(8);
   L.sort_key = take(4 * np);
   L.sort_rank = take(4 * np);
   L.pos_tmp = take(12 * np);
@@ -455,6 +457,7 @@ pm_status ctx_setup(pm_ctx* c, const pm_params* params, char* base, hipStream_t 
   c->scan_sums = reinterpret_cast<unsigned*>(base + L.scan_sums);
   c->slice_start = reinterpret_cast<unsigned*>(base + L.slice_start);
   c->chunks = reinterpret_cast<uint4*>(base + L.chunks);
+  c->pieces = reinterpret_cast<uint4*>(base + L.pieces);
   c->used = reinterpret_cast<unsigned*>(base + L.used);
   c->sort_key = reinterpret_cast<unsigned*>(base + L.sort_key);
   c->sort_rank = reinterpret_cast<unsigned*>(base + L.sort_rank);
@@ -464,6 +467,8 @@ pm_status ctx_setup(pm_ctx* c, const pm_params* params, char* base, hipStream_t 
   c->tiles = tile_count(c->logn);
   c->tmap.chunks = c->chunks;
   c->tmap.used = c->used;
+  c->tmap.pieces = c->pieces;
+  c->tmap.used_pieces = c->used + 1;
   c->tmap.tiles = c->tiles;
   c->sorted = false;
   c->q_blocks = qpot_blocks(c->logn);
@@ -665,7 +670,7 @@ pm_status sort_into(pm_ctx* c, const void* pos, const float* vel, const int32_t*
   }));
   PM_TRY(timed(c, kcSortScan, [&] {
     return launch_sort_scan(c->tile_counts, c->tiles, c->scan_sums, c->slice_start, c->chunks,
-                            c->used, c->stream);
+                            c->pieces, c->used, c->stream);
   }));
   PM_TRY(timed(c, kcSortScatter, [&] {
     return launch_sort_scatter(pos, vel, ids, c->np, c->sort_key, c->sort_rank, c->slice_start,
@@ -1045,8 +1050,8 @@ pm_status pm_spline_qforce(pm_ctx* c, const void* d_pos, const float* d_q, doubl
   if (!c || !d_pos || !d_q || !d_acc) return PM_EINVAL;
   if (!spline_h_ok(c, h)) return PM_EINVAL;
   return timed(c, kcSplineForce, [&] {
-    return launch_spline_qforce(c->fixed, c->logn, d_pos, c->np, d_q, (float)h, d_acc,
-                                c->stream);
+    return launch_spline_qforce(c->fixed, c->logn, d_pos, c->np, d_q, (float)h,
+                                c->sorted ? &c->tmap : nullptr, d_acc, c->stream);
   });
 }
 
@@ -1076,8 +1081,8 @@ pm_status pm_spline_step(pm_ctx* c, void* d_pos, float* d_vel, const double* tim
       });
     PM_TRY(run_qpot(c, c->delta, c->fixed, kOutQ));
     return timed(c, kcSplineForce, [&] {
-      return launch_spline_qforce(c->fixed, c->logn, d_pos, c->np, c->q, (float)h, gq,
-                                  c->stream);
+      return launch_spline_qforce(c->fixed, c->logn, d_pos, c->np, c->q, (float)h,
+                                  c->sorted ? &c->tmap : nullptr, gq, c->stream);
     });
   };
   auto kick_by = [&](const Kick& k) {
@@ -1340,7 +1345,7 @@ pm_status pm_batch_step(pm_batch* b, void* d_pos, float* d_vel, int32_t nactive,
     PM_TRY(dev(launch_sort_count(c->fixed, d_pos, c->np, c->logn, c->tile_counts, c->sort_key,
                                  c->sort_rank, c->stream, bt)));
     PM_TRY(dev(launch_sort_scan(c->tile_counts, c->tiles, c->scan_sums, c->slice_start, c->chunks,
-                                c->used, c->stream, bt)));
+                                c->pieces, c->used, c->stream, bt)));
     PM_TRY(dev(launch_sort_scatter(d_pos, d_vel, nullptr, c->np, c->sort_key, c->sort_rank,
                                    c->slice_start, c->pos_tmp, c->vel_tmp, nullptr, c->stream,
                                    bt)));

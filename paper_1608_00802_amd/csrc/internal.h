@@ -70,7 +70,7 @@ constexpr int kSlices = 16;
 // Counters of one slice are count_stride(tiles) apart (a multiple of 32
 // counters: the slices of a tile sit in different 128-byte lines).
 __host__ __device__ constexpr int count_stride(int tiles) { return (tiles + 31) & ~31; }
-// Blocks of the two scan kernels (256 tiles each), and their scratch of two
+// Blocks of the two scan kernels (256 tiles each), and their scratch of three
 // counters per block.
 __host__ __device__ constexpr int scan_blocks(int tiles) { return (tiles + 255) / 256; }
 __host__ __device__ constexpr int tile_lx(int logn) { return logn < kTileLX ? logn : kTileLX; }
@@ -200,11 +200,26 @@ hipError_t launch_deposit_f32(const float* pos, int64_t np, int logn, float* acc
                               hipStream_t s, const Batch& bt = Batch());
 // Tiled variants.  The particle sort leaves the list of chunks: chunk k holds
 // the particles [y, z) of tile x (at most kChunk of them), *used chunks in all.
+// The spline kernels, a hundred times the work per particle, take pieces in
+// the same form: a tile's particles in even shares of about kPiece, so that a
+// few dense tiles still fill the chip (10^6 particles in one object at 128^3
+// are 150 chunks but 490 pieces).
 struct TileMap {
   const uint4* chunks;
   const unsigned* used;
+  const uint4* pieces;
+  const unsigned* used_pieces;
   int tiles;
 };
+constexpr unsigned kPiece = 2048;
+__host__ __device__ constexpr unsigned piece_count(unsigned c) {
+  return c == 0 ? 0 : (c + kPiece / 2) / kPiece > 1 ? (c + kPiece / 2) / kPiece : 1;
+}
+// upper bound of the number of pieces (two or more of them hold at least
+// 3/4 kPiece particles each)
+inline unsigned piece_bound(int64_t np, int tiles) {
+  return (unsigned)(tiles + np / (kPiece / 4 * 3));
+}
 // upper bound of the number of chunks: every chunk is full except one per tile
 inline unsigned tiled_grid(int64_t np, int tiles) {
   return (unsigned)(tiles + (np + kChunk - 1) / kChunk);
@@ -237,11 +252,12 @@ hipError_t launch_deposit_f32_tiled(const float* pos, int64_t np, int logn, cons
 hipError_t launch_sort_count(bool fixed, const void* pos, int64_t np, int logn,
                              unsigned* counts, unsigned* key, unsigned* rank, hipStream_t s,
                              const Batch& bt = Batch());
-// slice_start: [tiles * kSlices + 1]; chunks, used: the TileMap's lists;
-// sums: scratch of 2 * scan_blocks(tiles) counters
+// slice_start: [tiles * kSlices + 1]; chunks, pieces: the TileMap's lists,
+// used[0], used[1] their lengths; sums: scratch of 3 * scan_blocks(tiles)
+// counters
 hipError_t launch_sort_scan(const unsigned* counts, int tiles, unsigned* sums,
-                            unsigned* slice_start, uint4* chunks, unsigned* used,
-                            hipStream_t s, const Batch& bt = Batch());
+                            unsigned* slice_start, uint4* chunks, uint4* pieces,
+                            unsigned* used, hipStream_t s, const Batch& bt = Batch());
 hipError_t launch_sort_scatter(const void* pos, const float* vel, const int* ids, int64_t np,
                                const unsigned* key, const unsigned* rank,
                                const unsigned* slice_start, uint32_t* pos_out, float* vel_out,
@@ -312,7 +328,8 @@ hipError_t launch_fft_x_power(int logn, const float2* spec, const float2* tw, in
 hipError_t launch_spline_deposit(bool fixed, int logn, const void* pos, int64_t np, float h,
                                  const TileMap* tm, unsigned long long* mass, hipStream_t s);
 hipError_t launch_spline_qforce(bool fixed, int logn, const void* pos, int64_t np,
-                                const float* q, float h, float* acc, hipStream_t s);
+                                const float* q, float h, const TileMap* tm, float* acc,
+                                hipStream_t s);
 // The spline step's half-kick (v += fg g_phi + fq g_q) and drift (x += fd v).
 hipError_t launch_spline_kick(float* vel, const float* gphi, const float* gq, int64_t np,
                               float fg, float fq, hipStream_t s);

@@ -132,39 +132,34 @@ __global__ void __launch_bounds__(kCountBlock) k_sort_count(const void* __restri
   }
 }
 
-// Exclusive block-wide prefix sums of (a, b) over kScanBlock threads; also
+// Exclusive block-wide prefix sums of v[0..2] over kScanBlock threads; also
 // returns the block totals.
-__device__ __forceinline__ void block_scan2(unsigned& a, unsigned& b, unsigned& ta,
-                                            unsigned& tb) {
-  __shared__ unsigned wa[kScanBlock / 64], wb[kScanBlock / 64];
+__device__ __forceinline__ void block_scan3(unsigned v[3], unsigned tot[3]) {
+  __shared__ unsigned ws[3][kScanBlock / 64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  unsigned ia = a, ib = b;
+  unsigned inc[3];
 #pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const unsigned va = __shfl_up(ia, off, 64), vb = __shfl_up(ib, off, 64);
-    if (lane >= off) {
-      ia += va;
-      ib += vb;
+  for (int j = 0; j < 3; ++j) {
+    inc[j] = v[j];
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const unsigned up = __shfl_up(inc[j], off, 64);
+      if (lane >= off) inc[j] += up;
     }
-  }
-  if (lane == 63) {
-    wa[w] = ia;
-    wb[w] = ib;
+    if (lane == 63) ws[j][w] = inc[j];
   }
   __syncthreads();
-  unsigned pa = 0, pb = 0;
-  ta = tb = 0;
 #pragma unroll
-  for (int k = 0; k < kScanBlock / 64; ++k) {
-    if (k < w) {
-      pa += wa[k];
-      pb += wb[k];
+  for (int j = 0; j < 3; ++j) {
+    unsigned before = 0;
+    tot[j] = 0;
+#pragma unroll
+    for (int k = 0; k < kScanBlock / 64; ++k) {
+      if (k < w) before += ws[j][k];
+      tot[j] += ws[j][k];
     }
-    ta += wa[k];
-    tb += wb[k];
+    v[j] = before + inc[j] - v[j];
   }
-  a = pa + ia - a;
-  b = pb + ib - b;
   __syncthreads();
 }
 
@@ -180,7 +175,7 @@ __device__ __forceinline__ unsigned tile_total(const unsigned* counts, int cstri
   return tot;
 }
 
-// Per block of kScanBlock tiles: particle and chunk totals.
+// Per block of kScanBlock tiles: particle, chunk and piece totals.
 __global__ void __launch_bounds__(kScanBlock) k_sort_scan_reduce(const unsigned* __restrict__ counts,
                                                                 int tiles, int cstride,
                                                                 unsigned* __restrict__ sums,
@@ -191,26 +186,24 @@ __global__ void __launch_bounds__(kScanBlock) k_sort_scan_reduce(const unsigned*
     sums = woff(sums, bt, sl);
   }
   const int t = blockIdx.x * kScanBlock + threadIdx.x;
-  unsigned a = 0, b = 0;
+  unsigned v[3] = {0, 0, 0}, tot[3];
   if (t < tiles) {
-    a = tile_total(counts, cstride, t, nullptr);
-    b = (a + kChunk - 1) / kChunk;
+    v[0] = tile_total(counts, cstride, t, nullptr);
+    v[1] = (v[0] + kChunk - 1) / kChunk;
+    v[2] = piece_count(v[0]);
   }
-  unsigned ta, tb;
-  block_scan2(a, b, ta, tb);
-  if (threadIdx.x == 0) {
-    sums[2 * blockIdx.x] = ta;
-    sums[2 * blockIdx.x + 1] = tb;
-  }
+  block_scan3(v, tot);
+  if (threadIdx.x < 3) sums[3 * blockIdx.x + threadIdx.x] = tot[threadIdx.x];
 }
 
 // Down-sweep: offsets of the earlier blocks, then per-tile prefix sums and
-// the tile's entries of the chunk list.
+// the tile's entries of the chunk and piece lists.
 __global__ void __launch_bounds__(kScanBlock) k_sort_scan_down(const unsigned* __restrict__ counts,
                                                               int tiles, int cstride,
                                                               const unsigned* __restrict__ sums,
                                                               unsigned* __restrict__ slice_start,
                                                               uint4* __restrict__ chunks,
+                                                              uint4* __restrict__ pieces,
                                                               unsigned* __restrict__ used,
                                                               Batch bt) {
   {
@@ -219,43 +212,44 @@ __global__ void __launch_bounds__(kScanBlock) k_sort_scan_down(const unsigned* _
     sums = woff(sums, bt, sl);
     slice_start = woff(slice_start, bt, sl);
     chunks = woff(chunks, bt, sl);
+    pieces = woff(pieces, bt, sl);
     used = woff(used, bt, sl);
   }
-  __shared__ unsigned off[2];
+  __shared__ unsigned off[3];
   if (threadIdx.x < 64) {
-    unsigned pa = 0, pb = 0;
-    for (int k = threadIdx.x; k < (int)blockIdx.x; k += 64) {
-      pa += sums[2 * k];
-      pb += sums[2 * k + 1];
-    }
+    unsigned p[3] = {0, 0, 0};
+    for (int k = threadIdx.x; k < (int)blockIdx.x; k += 64)
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      pa += __shfl_xor(pa, o, 64);
-      pb += __shfl_xor(pb, o, 64);
-    }
-    if (threadIdx.x == 0) {
-      off[0] = pa;
-      off[1] = pb;
-    }
+      for (int j = 0; j < 3; ++j) p[j] += sums[3 * k + j];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) p[j] += __shfl_xor(p[j], o, 64);
+    if (threadIdx.x == 0)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) off[j] = p[j];
   }
   __syncthreads();
   const int t = blockIdx.x * kScanBlock + threadIdx.x;
   unsigned c[kSlices];
-  unsigned a = 0, b = 0;
+  unsigned v[3] = {0, 0, 0}, tot[3], n = 0;
   if (t < tiles) {
-    a = tile_total(counts, cstride, t, c);
-    b = (a + kChunk - 1) / kChunk;
+    n = tile_total(counts, cstride, t, c);
+    v[0] = n;
+    v[1] = (n + kChunk - 1) / kChunk;
+    v[2] = piece_count(n);
   }
-  unsigned ta, tb;
-  block_scan2(a, b, ta, tb);
-  a += off[0];
-  b += off[1];
-  if (t < tiles) {
-    unsigned tot = 0;
+  const unsigned np_t = v[2];
+  block_scan3(v, tot);
 #pragma unroll
-    for (int s = 0; s < kSlices; ++s) tot += c[s];
-    for (unsigned p = a; p < a + tot; p += kChunk)
-      chunks[b++] = make_uint4((unsigned)t, p, min(p + (unsigned)kChunk, a + tot), 0u);
+  for (int j = 0; j < 3; ++j) v[j] += off[j];
+  const unsigned a = v[0], e = a + n;
+  if (t < tiles) {
+    for (unsigned p = a, k = v[1]; p < e; p += kChunk, ++k)
+      chunks[k] = make_uint4((unsigned)t, p, min(p + (unsigned)kChunk, e), 0u);
+    const unsigned share = np_t ? (n + np_t - 1) / np_t : 0;
+    for (unsigned k = 0; k < np_t; ++k)
+      pieces[v[2] + k] = make_uint4((unsigned)t, min(a + k * share, e), min(a + (k + 1) * share, e), 0u);
     unsigned r = a;
     uint4* s4 = reinterpret_cast<uint4*>(slice_start + (size_t)t * kSlices);
 #pragma unroll
@@ -270,8 +264,9 @@ __global__ void __launch_bounds__(kScanBlock) k_sort_scan_down(const unsigned* _
     }
   }
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-    slice_start[(size_t)tiles * kSlices] = off[0] + ta;
-    *used = off[1] + tb;
+    slice_start[(size_t)tiles * kSlices] = off[0] + tot[0];
+    used[0] = off[1] + tot[1];
+    used[1] = off[2] + tot[2];
   }
 }
 
@@ -326,13 +321,13 @@ hipError_t launch_sort_count(bool fixed, const void* pos, int64_t np, int logn,
 }
 
 hipError_t launch_sort_scan(const unsigned* counts, int tiles, unsigned* sums,
-                            unsigned* slice_start, uint4* chunks, unsigned* used,
-                            hipStream_t s, const Batch& bt) {
+                            unsigned* slice_start, uint4* chunks, uint4* pieces,
+                            unsigned* used, hipStream_t s, const Batch& bt) {
   const dim3 g(scan_blocks(tiles), bt.count);
   const int cs = count_stride(tiles);
   hipLaunchKernelGGL(k_sort_scan_reduce, g, dim3(kScanBlock), 0, s, counts, tiles, cs, sums, bt);
   hipLaunchKernelGGL(k_sort_scan_down, g, dim3(kScanBlock), 0, s, counts, tiles, cs, sums,
-                     slice_start, chunks, used, bt);
+                     slice_start, chunks, pieces, used, bt);
   return hipGetLastError();
 }
 

@@ -81,3 +81,66 @@ def test_tiled_step_equals_direct_step(pm, gpu, n, npart, move):
         torch.cuda.synchronize()
         out.append(_rows(pos, vel))
     assert np.array_equal(out[0], out[1])
+
+
+def _spline_nodes(x, n, h):
+    """(node index, offset vectors, r) of every node within reach, FP64."""
+    i = np.floor(x).astype(np.int64)
+    f = x - i
+    reach = np.arange(-int(h), int(h) + 2)
+    o = np.stack(np.meshgrid(reach, reach, reach, indexing="ij"), -1).reshape(-1, 3)
+    d = o[None] - f[:, None]
+    at = (i[:, None] + o[None]) % n
+    return (at[..., 0] * n + at[..., 1]) * n + at[..., 2], d, np.sqrt((d * d).sum(-1))
+
+
+@pytest.mark.parametrize("h", [2.0, 2.5, 2.7, 3.5, 4.0, 4.4, 5.0, 5.3])
+@pytest.mark.parametrize("n,npart", [(16, 37), (32, 700)])
+def test_spline_reach_classes(pm, gpu, n, npart, h):
+    """Density and force at each class of supports, edges included: tiled (a
+    sorted context, most particles having left their tile since) against
+    direct (bitwise for the density) and against sums in FP64."""
+    import torch
+    st = _state(n, npart, seed=npart)
+    moved = _state(n, npart, seed=npart + 1)
+    lp = pm.make_params(n, npart, float(n), hbar_over_m=1.0)
+    rng = np.random.default_rng(n)
+    q = rng.standard_normal(n ** 3).astype(np.float32)
+    dens, force = [], []
+    for tiled in (False, True):
+        ctx = pm.PMContext(lp, device=gpu)
+        pos, vel = to_device(moved, gpu)
+        if tiled:   # a tile map of the same count; a third of the particles stay in it
+            first, _ = to_device(st, gpu)
+            first[:, ::3] = pos[:, ::3]
+            ids = torch.arange(npart, dtype=torch.int32, device=gpu)
+            ctx.sort(first, vel, ids)
+            pos = pos[:, ids.long()].contiguous()
+        delta = torch.empty(n ** 3, dtype=torch.float32, device=gpu)
+        acc = torch.empty((3, npart), dtype=torch.float32, device=gpu)
+        ctx.spline_density(pos, delta, h)
+        mass = ctx.workspace[: 8 * n ** 3].view(torch.int64).clone()
+        ctx.spline_qforce(pos, torch.from_numpy(q).to(gpu), acc, h)
+        torch.cuda.synchronize()
+        if tiled:
+            back = torch.empty_like(acc)
+            back[:, ids.long()] = acc
+            acc = back
+        dens.append(mass.cpu().numpy())
+        force.append(acc.cpu().numpy().T.astype(np.float64))
+    assert np.array_equal(dens[0], dens[1])
+    at, d, r = _spline_nodes(moved.pos, n, h)
+    s = r / h
+    c = 8 / (np.pi * h ** 3)
+    w = np.where(s <= 0.5, 1 - 6 * s ** 2 + 6 * s ** 3, 2 * np.clip(1 - s, 0, None) ** 3)
+    ref = np.bincount(at.ravel(), c * w.ravel(), minlength=n ** 3) * 2.0 ** 40
+    hits = np.bincount(at.ravel(), (s < 1).ravel(), minlength=n ** 3)
+    # a kernel value takes a few roundings of q <= 1, times a slope below 2:
+    # 2^-20 of its maximum c, plus the rounding to integer units
+    assert np.all(np.abs(dens[0] - ref) <= hits * (2.0 ** -20 * c * 2.0 ** 40 + 1.0))
+    slope = np.where(s <= 0.5, -12 * s + 18 * s ** 2, -6 * np.clip(1 - s, 0, None) ** 2)
+    term = (q[at] * c / h * slope / np.maximum(r, 1e-30))[..., None] * d
+    # sums of fewer than 1500 terms in any order, a few roundings in each
+    bound = 1500 * 2.0 ** -24 * np.abs(term).sum(1) + 1e-12
+    for g in force:
+        assert np.all(np.abs(g - term.sum(1)) <= bound)
