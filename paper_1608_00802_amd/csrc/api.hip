@@ -1067,9 +1067,15 @@ pm_status pm_spline_step(pm_ctx* c, void* d_pos, float* d_vel, const double* tim
   // gradient of Q, [3][Np] floats each in the particle copy buffers
   float* gphi = reinterpret_cast<float*>(c->pos_tmp);
   float* gq = c->vel_tmp;
-  auto forces = [&]() -> pm_status {
+  // On a sorted context with quantum pressure both forces, the kicks and the
+  // drift are one pass over the particles.
+  const bool fused = c->sorted && c->has_q && spline_step_fused((float)h);
+  auto fields = [&]() -> pm_status {
     PM_TRY(run_spline_density(c, d_pos, h));
     PM_TRY(run_poisson(c, kSrcMass64, c->mass));
+    return c->has_q ? run_qpot(c, c->delta, c->fixed, kOutQ) : PM_OK;
+  };
+  auto forces = [&]() -> pm_status {
     PM_TRY(timed(c, kcForce, [&] {
       return launch_force(c->fixed, false, c->logn, d_pos, c->phi, c->q, c->np, 1.0f, 0.0f,
                           gphi, c->stream);
@@ -1079,7 +1085,6 @@ pm_status pm_spline_step(pm_ctx* c, void* d_pos, float* d_vel, const double* tim
       return timed(c, kcFill, [&] {
         return launch_fill_zero(gq, (12 * (size_t)c->np + 15) & ~(size_t)15, c->stream);
       });
-    PM_TRY(run_qpot(c, c->delta, c->fixed, kOutQ));
     return timed(c, kcSplineForce, [&] {
       return launch_spline_qforce(c->fixed, c->logn, d_pos, c->np, c->q, (float)h,
                                   c->sorted ? &c->tmap : nullptr, gq, c->stream);
@@ -1091,16 +1096,37 @@ pm_status pm_spline_step(pm_ctx* c, void* d_pos, float* d_vel, const double* tim
     });
   };
   c->fields_at_pos = false;
-  PM_TRY(forces());
-  for (int s = 0; s < nsteps; ++s) {
-    const double t0 = times[s], t1 = times[s + 1], tm = midpoint(c->p, t0, t1);
-    PM_TRY(kick_by(kick(c->p, t0, tm)));
-    PM_TRY(timed(c, kcGatherKD, [&] {
-      return launch_spline_drift(c->fixed, c->logn, d_pos, d_vel, c->np, drift(c->p, t0, t1),
-                                 c->stream);
-    }));
-    PM_TRY(forces());
-    PM_TRY(kick_by(kick(c->p, tm, t1)));
+  Kick close = {0.0, 0.0};
+  for (int s = 0; s <= nsteps; ++s) {
+    // fields at times[s]; the closing half-kick of step s - 1, then the
+    // opening half-kick and the drift of step s
+    PM_TRY(fields());
+    Kick open = {0.0, 0.0}, next = {0.0, 0.0};
+    double fd = 0.0;
+    if (s < nsteps) {
+      const double t0 = times[s], t1 = times[s + 1], tm = midpoint(c->p, t0, t1);
+      open = kick(c->p, t0, tm);
+      next = kick(c->p, tm, t1);
+      fd = drift(c->p, t0, t1);
+    }
+    if (fused) {
+      const SplineKicks k = {(float)close.g, (float)close.q, (float)open.g, (float)open.q,
+                             fd, s > 0, s < nsteps};
+      PM_TRY(timed(c, kcSplineForce, [&] {
+        return launch_spline_push(c->fixed, c->logn, d_pos, d_vel, c->np, c->phi, c->q, (float)h,
+                                  c->tmap, k, c->stream);
+      }));
+    } else {
+      PM_TRY(forces());
+      if (s > 0) PM_TRY(kick_by(close));
+      if (s < nsteps) {
+        PM_TRY(kick_by(open));
+        PM_TRY(timed(c, kcGatherKD, [&] {
+          return launch_spline_drift(c->fixed, c->logn, d_pos, d_vel, c->np, fd, c->stream);
+        }));
+      }
+    }
+    close = next;
   }
   // delta holds the spline contrast and phi, Q its fields; none of them is
   // what the cloud-in-cell calls expect

@@ -77,50 +77,6 @@ __device__ __forceinline__ void load_particle(const void* __restrict__ pos,
   }
 }
 
-// Interpolated -2 grad F at one particle.  at(a, b, c) returns F at offsets
-// (a - 1, b - 1, c - 1) from the particle's base cell, a, b, c in 0..3.
-// Central differences at the 8 CIC nodes use the 2x2x2 core and, per axis,
-// the two planes outside it; each axis' extra nodes are consumed as soon as
-// they are read, so only the core stays live.  The trilinear weights are
-// applied as nested linear interpolations (22 instructions per axis); the
-// fused multiply-adds are written out so that every kernel rounds alike.
-__device__ __forceinline__ float lerp_f(float lo, float hi, float f) {
-  return fmaf(f, hi - lo, lo);
-}
-template <typename At>
-__device__ __forceinline__ void interp_grad(const float f[3], At&& at, float g[3]) {
-  float core[2][2][2], e[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int c = 0; c < 2; ++c) core[a][b][c] = at(1 + a, 1 + b, 1 + c);
-  // the node at x offset 0 takes F(+1) - F(-1) = core[1] - plane -1, the one
-  // at offset 1 the plane at +2 minus core[0]; here with the opposite sign
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-      e[b][c] = lerp_f(at(0, 1 + b, 1 + c) - core[1][b][c], core[0][b][c] - at(3, 1 + b, 1 + c),
-                       f[0]);
-  g[0] = lerp_f(lerp_f(e[0][0], e[0][1], f[2]), lerp_f(e[1][0], e[1][1], f[2]), f[1]);
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-      e[a][c] = lerp_f(at(1 + a, 0, 1 + c) - core[a][1][c], core[a][0][c] - at(1 + a, 3, 1 + c),
-                       f[1]);
-  g[1] = lerp_f(lerp_f(e[0][0], e[0][1], f[2]), lerp_f(e[1][0], e[1][1], f[2]), f[0]);
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-      e[a][b] = lerp_f(at(1 + a, 1 + b, 0) - core[a][b][1], core[a][b][0] - at(1 + a, 1 + b, 3),
-                       f[2]);
-  g[2] = lerp_f(lerp_f(e[0][0], e[0][1], f[1]), lerp_f(e[1][0], e[1][1], f[1]), f[0]);
-}
-
 // Low 32 bits of rint(a * b), ties to even: the drift in fixed-point units,
 // wrapped.  For |a * b| < 2^51 (a drift below 2^19 box lengths), adding
 // 1.5 * 2^52 rounds the product to an integer and leaves it, two's

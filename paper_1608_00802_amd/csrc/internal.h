@@ -330,7 +330,20 @@ hipError_t launch_spline_deposit(bool fixed, int logn, const void* pos, int64_t 
 hipError_t launch_spline_qforce(bool fixed, int logn, const void* pos, int64_t np,
                                 const float* q, float h, const TileMap* tm, float* acc,
                                 hipStream_t s);
-// The spline step's half-kick (v += fg g_phi + fq g_q) and drift (x += fd v).
+// One pass of the spline step over the particles of a sorted context: both
+// forces at the current positions, the closing half-kick of the previous step
+// (if close), the opening half-kick and the drift of the next (if open).  For
+// the supports that spline_step_fused accepts.
+struct SplineKicks {
+  float close_g, close_q, open_g, open_q;
+  double drift;
+  bool close, open;
+};
+bool spline_step_fused(float h);
+hipError_t launch_spline_push(bool fixed, int logn, void* pos, float* vel, int64_t np,
+                              const float* phi, const float* q, float h, const TileMap& tm,
+                              const SplineKicks& k, hipStream_t s);
+// Otherwise, the step's half-kick (v += fg g_phi + fq g_q) and drift (x += fd v).
 hipError_t launch_spline_kick(float* vel, const float* gphi, const float* gq, int64_t np,
                               float fg, float fq, hipStream_t s);
 hipError_t launch_spline_drift(bool fixed, int logn, void* pos, const float* vel, int64_t np,

@@ -16,6 +16,7 @@
 // from -1), which is what the FP64 path of the Q stencil reads there.
 #include <utility>
 
+#include "cic.h"
 #include "internal.h"
 
 namespace fdm {
@@ -272,13 +273,13 @@ __host__ __device__ constexpr int spline_window(int logn) {
          ((1 << tile_lz(logn)) + Reach<H2>::SPAN - 1);
 }
 
-// The tile of a piece and its window's geometry.
-template <int H2>
-struct SplineTile {
-  static constexpr int E = Reach<H2>::SPAN - 1;
+// The tile of a piece and the geometry of a window with BEFORE cells in front
+// of it and E - BEFORE behind, on each axis.
+template <int BEFORE, int E>
+struct TileWindow {
   static constexpr int WX = (1 << kTileLX) + E, WY = (1 << kTileLY) + E;
   int o[3], tz, wz;
-  __device__ __forceinline__ SplineTile(int logn, int tile) {
+  __device__ __forceinline__ TileWindow(int logn, int tile) {
     const int lz = tile_lz(logn), nty = logn - kTileLY, ntz = logn - lz;
     o[0] = (tile >> (nty + ntz)) << kTileLX;
     o[1] = ((tile >> ntz) & ((1 << nty) - 1)) << kTileLY;
@@ -291,7 +292,7 @@ struct SplineTile {
     const int mask = (1 << logn) - 1;
     const int rx = (i[0] - o[0]) & mask, ry = (i[1] - o[1]) & mask, rz = (i[2] - o[2]) & mask;
     if (rx >= (1 << kTileLX) || ry >= (1 << kTileLY) || rz >= tz) return -1;
-    return ((rx + Reach<H2>::R) * WY + ry + Reach<H2>::R) * wz + rz + Reach<H2>::R;
+    return ((rx + BEFORE) * WY + ry + BEFORE) * wz + rz + BEFORE;
   }
   // fn(window index, mesh index) for this thread's nodes of the window
   template <class F>
@@ -299,13 +300,19 @@ struct SplineTile {
     const int mask = (1 << logn) - 1;
     for (int row = threadIdx.x >> 6; row < WX * WY; row += kSplineBlock / 64) {
       const int lx = row / WY, ly = row % WY;
-      const int base = ((((o[0] - Reach<H2>::R + lx) & mask) << logn) +
-                        ((o[1] - Reach<H2>::R + ly) & mask)) << logn;
+      const int base = ((((o[0] - BEFORE + lx) & mask) << logn) +
+                        ((o[1] - BEFORE + ly) & mask)) << logn;
       const int z = threadIdx.x & 63;
-      if (z < wz) fn(row * wz + z, base + ((o[2] - Reach<H2>::R + z) & mask));
+      if (z < wz) fn(row * wz + z, base + ((o[2] - BEFORE + z) & mask));
     }
   }
 };
+template <int H2>
+using SplineTile = TileWindow<Reach<H2>::R, Reach<H2>::SPAN - 1>;
+using GradTile = TileWindow<1, 3>;   // the nodes of interp_grad
+__host__ __device__ constexpr int grad_window(int logn) {
+  return GradTile::WX * GradTile::WY * ((1 << tile_lz(logn)) + 3);
+}
 
 template <int H2>
 __global__ void __launch_bounds__(kSplineBlock, 4) k_spline_deposit_tiled(
@@ -442,31 +449,81 @@ __global__ void __launch_bounds__(kBlock) k_spline_qforce_fixed_reach(
   }
 }
 
+// The factors of one pass of the spline step over the particles: the closing
+// half-kick of the previous step, the opening one of the next and its drift.
+struct SplineStep {
+  float* vel;
+  const float* phi;
+  float cg, cq, og, oq;
+  double fd;
+  int close, open;
+};
+
+// v += fg g_phi + fq g_q, and the drift of one coordinate word: fixed point,
+// the displacement rounded to the nearest unit, 32-bit wrap; float, wrapped
+// into [0, N).
+__device__ __forceinline__ float spline_kick(float v, float gphi, float gq, float fg, float fq) {
+  return fmaf(fq, gq, fmaf(fg, gphi, v));
+}
+__device__ __forceinline__ uint32_t spline_drift(const SplinePos& sp, uint32_t raw, float v,
+                                                 double fd) {
+  if (sp.fixed) {
+    const double units = (double)v * fd * (double)(1ull << (32 - sp.logn));
+    return raw + (uint32_t)(int64_t)llrint(units);
+  }
+  const float n = (float)(1 << sp.logn);
+  float x = fmaf((float)fd, v, __uint_as_float(raw));
+  x -= n * floorf(x * (1.0f / n));
+  return __float_as_uint(x >= n ? 0.0f : x);
+}
+
 // Sorted context: Q of the piece's window staged in LDS.  Bound by its
 // arithmetic (11 to 14 instructions per node): 1.18 ms at 256^3 with one
 // particle per cell and h = 3.5, against 2.98 with per-particle spans and Q
 // read from the mesh; 10^6 particles in one object at 128^3: 0.17 against
 // 0.45 ms.
-template <int H2>
-__global__ void __launch_bounds__(kSplineBlock, H2 <= 7 ? 8 : 5) k_spline_qforce_tiled(
-    const uint32_t* __restrict__ pos, int64_t np, SplinePos sp, TileMap tm,
-    const float* __restrict__ qmesh, float inv_h, float coef, float* __restrict__ acc) {
+// STEP: also -grad phi from its own window, the kicks and the drift, so that
+// the particles' traffic (60 bytes each) runs under the arithmetic
+// (256^3, h = 3.5: 1.48 ms in place of 1.18 and 0.54 for the separate passes).
+template <int H2, bool STEP>
+__global__ void __launch_bounds__(kSplineBlock, H2 <= 7 && !STEP ? 8 : 5) k_spline_qforce_tiled(
+    uint32_t* __restrict__ pos, int64_t np, SplinePos sp, TileMap tm,
+    const float* __restrict__ qmesh, float inv_h, float coef, float* __restrict__ acc,
+    SplineStep st) {
   using Tile = SplineTile<H2>;
   extern __shared__ float qwin[];
+  float* pwin = qwin + spline_window<H2>(sp.logn);
   const unsigned used = __builtin_amdgcn_readfirstlane(*tm.used_pieces);
   for (unsigned b = blockIdx.x; b < used; b += gridDim.x) {
     const uint4 pc = tm.pieces[b];
     const Tile tile(sp.logn, (int)__builtin_amdgcn_readfirstlane(pc.x));
+    const GradTile gtile(sp.logn, (int)__builtin_amdgcn_readfirstlane(pc.x));
     const unsigned p1 = __builtin_amdgcn_readfirstlane(pc.z);
     tile.each(sp.logn, [&](int w, int node) { qwin[w] = qmesh[node]; });
+    if constexpr (STEP) gtile.each(sp.logn, [&](int w, int node) { pwin[w] = st.phi[node]; });
     __syncthreads();
     for (unsigned p = __builtin_amdgcn_readfirstlane(pc.y); p < p1; p += kSplineBlock) {
       const bool valid = p + threadIdx.x < p1;
       int i[3] = {0, 0, 0}, at = 0;
-      float f[3] = {0.0f, 0.0f, 0.0f}, g[3];
+      float f[3] = {0.0f, 0.0f, 0.0f}, g[3], gp[3], v[3];
       if (valid) {
         load_cell(sp, pos, np, p + threadIdx.x, i, f);
         at = tile.cell(sp.logn, i);
+        if constexpr (STEP) {
+          const int gat = gtile.cell(sp.logn, i) - (GradTile::WY + 1) * gtile.wz - 1;
+          const int mask = (1 << sp.logn) - 1;
+          if (at >= 0)
+            interp_grad(f, [&](int a, int bb, int c) {
+              return pwin[gat + (a * GradTile::WY + bb) * gtile.wz + c];
+            }, gp);
+          else
+            interp_grad(f, [&](int a, int bb, int c) {
+              return st.phi[((((((i[0] + a - 1) & mask) << sp.logn) + ((i[1] + bb - 1) & mask))
+                              << sp.logn)) + ((i[2] + c - 1) & mask)];
+            }, gp);
+#pragma unroll
+          for (int d = 0; d < 3; ++d) v[d] = st.vel[d * np + p + threadIdx.x];
+        }
       }
       if (valid && at >= 0) {
         const Folded<H2> fo(f, inv_h);
@@ -482,10 +539,10 @@ __global__ void __launch_bounds__(kSplineBlock, H2 <= 7 ? 8 : 5) k_spline_qforce
         float w[3] = {0.0f, 0.0f, 0.0f};
         each_node_wave<H2>(sp.logn, iu, fu, inv_h,
                            [&](int node, float x, float y, float z, float s) {
-          const float v = qmesh[node] * spline_g<true>(s);
-          w[0] = fmaf(v, x, w[0]);
-          w[1] = fmaf(v, y, w[1]);
-          w[2] = fmaf(v, z, w[2]);
+          const float t = qmesh[node] * spline_g<true>(s);
+          w[0] = fmaf(t, x, w[0]);
+          w[1] = fmaf(t, y, w[1]);
+          w[2] = fmaf(t, z, w[2]);
         });
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
@@ -493,9 +550,24 @@ __global__ void __launch_bounds__(kSplineBlock, H2 <= 7 ? 8 : 5) k_spline_qforce
           if ((int)(threadIdx.x & 63) == lane) g[d] = w[d];
         }
       });
-      if (valid)
+      if (valid) {
 #pragma unroll
-        for (int d = 0; d < 3; ++d) acc[d * np + p + threadIdx.x] = coef * g[d];
+        for (int d = 0; d < 3; ++d) {
+          const int64_t k = d * np + p + threadIdx.x;
+          const float gq = coef * g[d];
+          if constexpr (STEP) {
+            const float gphi = 0.5f * gp[d];
+            if (st.close) v[d] = spline_kick(v[d], gphi, gq, st.cg, st.cq);
+            if (st.open) {
+              v[d] = spline_kick(v[d], gphi, gq, st.og, st.oq);
+              pos[k] = spline_drift(sp, pos[k], v[d], st.fd);
+            }
+            st.vel[k] = v[d];
+          } else {
+            acc[k] = gq;
+          }
+        }
+      }
     }
     __syncthreads();
   }
@@ -508,30 +580,16 @@ __global__ void __launch_bounds__(kBlock) k_spline_kick(float* __restrict__ vel,
                                                         float fg, float fq) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-    vel[i] = fmaf(fq, gq[i], fmaf(fg, gphi[i], vel[i]));
+    vel[i] = spline_kick(vel[i], gphi[i], gq[i], fg, fq);
 }
 
-// Drift of the spline step: x += fd v, periodic.  Fixed point: the
-// displacement rounded to the nearest unit, 32-bit wrap; float: wrapped into
-// [0, N).
-template <int LOGN, bool FIXED>
-__global__ void __launch_bounds__(kBlock) k_spline_drift(void* __restrict__ pos,
+// Drift of the spline step: x += fd v, periodic.
+__global__ void __launch_bounds__(kBlock) k_spline_drift(uint32_t* __restrict__ pos,
                                                          const float* __restrict__ vel,
-                                                         int64_t n, double fd) {
-  constexpr int N = 1 << LOGN;
+                                                         int64_t n, SplinePos sp, double fd) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    if constexpr (FIXED) {
-      const double units = (double)vel[i] * fd * (double)(1ull << (32 - LOGN));
-      uint32_t* u = static_cast<uint32_t*>(pos);
-      u[i] += (uint32_t)(int64_t)llrint(units);
-    } else {
-      float* x = static_cast<float*>(pos);
-      float v = fmaf((float)fd, vel[i], x[i]);
-      v -= (float)N * floorf(v * (1.0f / (float)N));
-      x[i] = v >= (float)N ? 0.0f : v;
-    }
-  }
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
+    pos[i] = spline_drift(sp, pos[i], vel[i], fd);
 }
 
 unsigned spline_grid(int64_t n) {
@@ -572,6 +630,8 @@ int spline_class(float h) {
     case 10: MACRO(10); break;      \
     default: return hipErrorInvalidValue; \
   }
+
+float spline_force_coef(float h) { return (float)(-48.0 / (M_PI * (double)h * h * h * h)); }
 
 unsigned piece_grid(int64_t np, int tiles) {
   const unsigned bound = piece_bound(np, tiles);
@@ -619,17 +679,19 @@ hipError_t launch_spline_qforce(bool fixed, int logn, const void* pos, int64_t n
   spline_range(h, lo, hi);
   const SplinePos sp = spline_pos(fixed, logn);
   const uint32_t* words = static_cast<const uint32_t*>(pos);
-  const float coef = (float)(-48.0 / (M_PI * (double)h * h * h * h));
+  const float coef = spline_force_coef(h);
   const int h2 = spline_class(h);
   if (tm && h2) {
     const dim3 g(piece_grid(np, tm->tiles));
 #define T_(H2)                                                                                  \
   {                                                                                             \
     const int lds = 4 * spline_window<H2>(logn);                                                \
-    const hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_spline_qforce_tiled<H2>), lds); \
+    const hipError_t e =                                                                        \
+        allow_lds(reinterpret_cast<const void*>(&k_spline_qforce_tiled<H2, false>), lds);       \
     if (e != hipSuccess) return e;                                                              \
-    hipLaunchKernelGGL((k_spline_qforce_tiled<H2>), g, dim3(kSplineBlock), lds, s, words, np,   \
-                       sp, *tm, q, 1.0f / h, coef, acc);                                        \
+    hipLaunchKernelGGL((k_spline_qforce_tiled<H2, false>), g, dim3(kSplineBlock), lds, s,       \
+                       const_cast<uint32_t*>(words), np, sp, *tm, q, 1.0f / h, coef, acc,       \
+                       SplineStep());                                                           \
   }
     FDM_REACH_SWITCH(h2, T_)
 #undef T_
@@ -657,14 +719,32 @@ hipError_t launch_spline_kick(float* vel, const float* gphi, const float* gq, in
 hipError_t launch_spline_drift(bool fixed, int logn, void* pos, const float* vel, int64_t np,
                                double fd, hipStream_t s) {
   const int64_t n = 3 * np;
-  const unsigned g = spline_grid(n);
-#define L_(LN)                                                                               \
-  if (fixed)                                                                                 \
-    hipLaunchKernelGGL((k_spline_drift<LN, true>), dim3(g), dim3(kBlock), 0, s, pos, vel, n, fd); \
-  else                                                                                       \
-    hipLaunchKernelGGL((k_spline_drift<LN, false>), dim3(g), dim3(kBlock), 0, s, pos, vel, n, fd);
-  FDM_LOGN_SWITCH(logn, L_)
-#undef L_
+  hipLaunchKernelGGL(k_spline_drift, dim3(spline_grid(n)), dim3(kBlock), 0, s,
+                     static_cast<uint32_t*>(pos), vel, n, spline_pos(fixed, logn), fd);
+  return hipGetLastError();
+}
+
+bool spline_step_fused(float h) { return spline_class(h) != 0; }
+
+hipError_t launch_spline_push(bool fixed, int logn, void* pos, float* vel, int64_t np,
+                              const float* phi, const float* q, float h, const TileMap& tm,
+                              const SplineKicks& k, hipStream_t s) {
+  const SplinePos sp = spline_pos(fixed, logn);
+  const float coef = spline_force_coef(h);
+  const SplineStep st = {vel, phi, k.close_g, k.close_q, k.open_g, k.open_q,
+                         k.drift, k.close, k.open};
+  const dim3 g(piece_grid(np, tm.tiles));
+#define T_(H2)                                                                                  \
+  {                                                                                             \
+    const int lds = 4 * (spline_window<H2>(logn) + grad_window(logn));                          \
+    const hipError_t e =                                                                        \
+        allow_lds(reinterpret_cast<const void*>(&k_spline_qforce_tiled<H2, true>), lds);        \
+    if (e != hipSuccess) return e;                                                              \
+    hipLaunchKernelGGL((k_spline_qforce_tiled<H2, true>), g, dim3(kSplineBlock), lds, s,        \
+                       static_cast<uint32_t*>(pos), np, sp, tm, q, 1.0f / h, coef, nullptr, st); \
+  }
+  FDM_REACH_SWITCH(spline_class(h), T_)
+#undef T_
   return hipGetLastError();
 }
 

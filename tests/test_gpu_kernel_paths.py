@@ -144,3 +144,32 @@ def test_spline_reach_classes(pm, gpu, n, npart, h):
     bound = 1500 * 2.0 ** -24 * np.abs(term).sum(1) + 1e-12
     for g in force:
         assert np.all(np.abs(g - term.sum(1)) <= bound)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("n,npart,h", [(16, 1, 2.0), (16, 2500, 3.5), (32, 6000, 4.6)])
+def test_spline_push_equals_separate_passes(pm, gpu, n, npart, h, prec):
+    """One pass for both forces, kicks and drift (sorted context) against the
+    separate kernels (unsorted): the same sums in the same order, so they
+    differ by the contraction of a few roundings of partial sums at most."""
+    import torch
+    st = _state(n, npart, seed=npart, clumps=False)
+    lp = pm.make_params(n, npart, float(n), hbar_over_m=0.5, precision=prec)
+    out = []
+    for fused in (False, True):
+        ctx = pm.PMContext(lp, device=gpu)
+        pos, vel = to_device(st, gpu, fp32_positions=prec == 0)
+        ids = torch.arange(npart, dtype=torch.int32, device=gpu)
+        if fused:
+            ctx.sort(pos, vel, ids)
+        ctx.spline_step(pos, vel, [0.0, 0.01, 0.03], h)
+        torch.cuda.synchronize()
+        p, v = torch.empty_like(pos), torch.empty_like(vel)
+        p[:, ids.long()], v[:, ids.long()] = pos, vel
+        x = p.double() * (n / 2.0 ** 32 if prec else 1.0)
+        out.append((x.cpu().numpy(), v.cpu().numpy().astype(np.float64)))
+    kick = max(np.abs(out[0][1] - st.vel32.astype(np.float64)).max(), 1e-6)
+    assert np.abs(out[1][1] - out[0][1]).max() <= 2.0 ** -16 * kick + 2.0 ** -22
+    # a position word is one rounding of the drift on top
+    d = (out[1][0] - out[0][0] + n / 2) % n - n / 2
+    assert np.abs(d).max() <= 0.03 * (2.0 ** -16 * kick + 2.0 ** -22) + 2.0 ** -22 * n
