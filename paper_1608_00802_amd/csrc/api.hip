@@ -70,10 +70,8 @@ struct pm_ctx {
   unsigned* tile_counts;  // [kSlices][count_stride(tiles)]
   unsigned* scan_sums;    // [3 * scan_blocks(tiles)]
   unsigned* slice_start;  // [tiles * kSlices + 1]
-  uint4* chunks;          // the tile map's chunk and piece lists, valid once sorted
-  uint4* pieces;
-  unsigned* used;         // their lengths
   TileMap tmap;
+  TileMap bin_map;        // of positions binned for one deposit (pos_tmp)
   unsigned* sort_key;
   unsigned* sort_rank;
   uint32_t* pos_tmp;
@@ -139,7 +137,7 @@ int ilog2_exact(int n) {
 
 struct Layout {
   size_t mass, delta, phi, q, spec, tw, s2, partials, kpart, result, tile_counts, scan_sums,
-      slice_start, chunks, pieces, used, sort_key, sort_rank, pos_tmp, vel_tmp, ids_tmp, total;
+      slice_start, chunks, pieces, used, bin_chunks, bin_pieces, bin_used, sort_key, sort_rank, pos_tmp, vel_tmp, ids_tmp, total;
 };
 
 Layout layout_for(const pm_params& p) {
@@ -174,6 +172,9 @@ Layout layout_for(const pm_params& p) {
   L.chunks = take(sizeof(uint4) * (size_t)tiled_grid((int64_t)np, (int)tiles));
   L.pieces = take(sizeof(uint4) * (size_t)piece_bound((int64_t)np, (int)tiles));
   L.used = take(8);
+  L.bin_chunks = take(sizeof(uint4) * (size_t)tiled_grid((int64_t)np, (int)tiles));
+  L.bin_pieces = take(sizeof(uint4) * (size_t)piece_bound((int64_t)np, (int)tiles));
+  L.bin_used = take(8);
   L.sort_key = take(4 * np);
   L.sort_rank = take(4 * np);
   L.pos_tmp = take(12 * np);
@@ -321,22 +322,69 @@ double midpoint(const pm_params& p, double t0, double t1) {
 }
 
 // ------------------------------------------------------------ launch sequences
-pm_status run_deposit(pm_ctx* c, const void* pos) {
+// Count, scan and scatter the particles into dst by tile (velocities and ids
+// where given); the tile map then describes dst.
+pm_status bin_into(pm_ctx* c, const TileMap& map, const void* pos, const float* vel,
+                   const int32_t* ids, uint32_t* dst_pos, float* dst_vel, int* dst_ids) {
+  const size_t cbytes = 4 * (size_t)kSlices * count_stride(c->tiles);
+  PM_TRY(timed(c, kcFill, [&] { return launch_fill_zero(c->tile_counts, cbytes, c->stream); }));
+  PM_TRY(timed(c, kcSortCount, [&] {
+    return launch_sort_count(c->fixed, pos, c->np, c->logn, c->tile_counts, c->sort_key,
+                             c->sort_rank, c->stream);
+  }));
+  PM_TRY(timed(c, kcSortScan, [&] {
+    return launch_sort_scan(c->tile_counts, c->tiles, c->scan_sums, c->slice_start, map,
+                            c->stream);
+  }));
+  return timed(c, kcSortScatter, [&] {
+    return launch_sort_scatter(pos, vel, ids, c->np, c->sort_key, c->sort_rank, c->slice_start,
+                               dst_pos, dst_vel, dst_ids, c->stream);
+  });
+}
+
+pm_status sort_into(pm_ctx* c, const void* pos, const float* vel, const int32_t* ids,
+                    uint32_t* dst_pos, float* dst_vel, int* dst_ids) {
+  PM_TRY(bin_into(c, c->tmap, pos, vel, ids, dst_pos, dst_vel, dst_ids));
+  c->sorted = true;
+  c->since_sort = 0;
+  return PM_OK;
+}
+
+// From this many particles on, positions in an order of the caller's are
+// binned by tile into the workspace for one deposit, which then runs from
+// LDS windows instead of adding to the mesh particle by particle (24 to 160
+// G adds/s, less where cells are dense).  Whole pm_deposit calls, direct
+// against binned: 256^3 in lattice order 1491 against 498 us, in clumps 4114
+// against 450; 128^3 250 against 83 and 775 against 91; 64^3 48 against 39.
+// Below, the six small launches cost more than they save for particles in
+// lattice order (32^3: 13 against 33 us) and about what they save in random
+// order (100003 at 64^3: 45 against 37).
+constexpr int64_t kBinMin = 1 << 17;
+
+// Deposit at pos, in the order of the tile map tm (null: in any order).
+pm_status run_deposit(pm_ctx* c, const void* pos, const TileMap* tm) {
   PM_TRY(timed(c, kcFill, [&] { return launch_fill_zero(c->mass, 8 * c->ncell + kStrayBytes, c->stream); }));
+  if (!tm && c->np >= kBinMin) {
+    PM_TRY(bin_into(c, c->bin_map, pos, nullptr, nullptr, c->pos_tmp, nullptr, nullptr));
+    pos = c->pos_tmp;
+    tm = &c->bin_map;
+  }
   return timed(c, kcDeposit, [&] {
-    if (c->fixed && c->sorted)
-      return launch_deposit_fixed_tiled(static_cast<const uint32_t*>(pos), c->np, c->logn,
-                                        c->tmap, static_cast<unsigned long long*>(c->mass),
-                                        c->stream);
+    if (c->fixed && tm)
+      return launch_deposit_fixed_tiled(static_cast<const uint32_t*>(pos), c->np, c->logn, *tm,
+                                        static_cast<unsigned long long*>(c->mass), c->stream);
     if (c->fixed)
       return launch_deposit_fixed(static_cast<const uint32_t*>(pos), c->np, c->logn,
                                   static_cast<unsigned long long*>(c->mass), c->stream);
-    if (c->sorted)
-      return launch_deposit_f32_tiled(static_cast<const float*>(pos), c->np, c->logn, c->tmap,
+    if (tm)
+      return launch_deposit_f32_tiled(static_cast<const float*>(pos), c->np, c->logn, *tm,
                                       static_cast<float*>(c->mass), c->stream);
     return launch_deposit_f32(static_cast<const float*>(pos), c->np, c->logn,
                               static_cast<float*>(c->mass), c->stream);
   });
+}
+pm_status run_deposit(pm_ctx* c, const void* pos) {
+  return run_deposit(c, pos, c->sorted ? &c->tmap : nullptr);
 }
 
 // Forward z-pass from the context's mass mesh (or from a given delta),
@@ -456,20 +504,22 @@ pm_status ctx_setup(pm_ctx* c, const pm_params* params, char* base, hipStream_t 
   c->tile_counts = reinterpret_cast<unsigned*>(base + L.tile_counts);
   c->scan_sums = reinterpret_cast<unsigned*>(base + L.scan_sums);
   c->slice_start = reinterpret_cast<unsigned*>(base + L.slice_start);
-  c->chunks = reinterpret_cast<uint4*>(base + L.chunks);
-  c->pieces = reinterpret_cast<uint4*>(base + L.pieces);
-  c->used = reinterpret_cast<unsigned*>(base + L.used);
   c->sort_key = reinterpret_cast<unsigned*>(base + L.sort_key);
   c->sort_rank = reinterpret_cast<unsigned*>(base + L.sort_rank);
   c->pos_tmp = reinterpret_cast<uint32_t*>(base + L.pos_tmp);
   c->vel_tmp = reinterpret_cast<float*>(base + L.vel_tmp);
   c->ids_tmp = reinterpret_cast<int*>(base + L.ids_tmp);
   c->tiles = tile_count(c->logn);
-  c->tmap.chunks = c->chunks;
-  c->tmap.used = c->used;
-  c->tmap.pieces = c->pieces;
-  c->tmap.used_pieces = c->used + 1;
-  c->tmap.tiles = c->tiles;
+  auto tile_map = [&](size_t chunks, size_t pieces, size_t used) {
+    TileMap m;
+    m.chunks = reinterpret_cast<uint4*>(base + chunks);
+    m.pieces = reinterpret_cast<uint4*>(base + pieces);
+    m.used = reinterpret_cast<unsigned*>(base + used);
+    m.tiles = c->tiles;
+    return m;
+  };
+  c->tmap = tile_map(L.chunks, L.pieces, L.used);
+  c->bin_map = tile_map(L.bin_chunks, L.bin_pieces, L.bin_used);
   c->sorted = false;
   c->q_blocks = qpot_blocks(c->logn);
   c->k_blocks = kinetic_blocks(c->np);
@@ -658,29 +708,6 @@ void poll_sort_stat(pm_ctx* c) {
 
 namespace {
 
-// Count, scan and scatter the particles (and ids) into dst by tile; the
-// tile map then describes dst.
-pm_status sort_into(pm_ctx* c, const void* pos, const float* vel, const int32_t* ids,
-                    uint32_t* dst_pos, float* dst_vel, int* dst_ids) {
-  const size_t cbytes = 4 * (size_t)kSlices * count_stride(c->tiles);
-  PM_TRY(timed(c, kcFill, [&] { return launch_fill_zero(c->tile_counts, cbytes, c->stream); }));
-  PM_TRY(timed(c, kcSortCount, [&] {
-    return launch_sort_count(c->fixed, pos, c->np, c->logn, c->tile_counts, c->sort_key,
-                             c->sort_rank, c->stream);
-  }));
-  PM_TRY(timed(c, kcSortScan, [&] {
-    return launch_sort_scan(c->tile_counts, c->tiles, c->scan_sums, c->slice_start, c->chunks,
-                            c->pieces, c->used, c->stream);
-  }));
-  PM_TRY(timed(c, kcSortScatter, [&] {
-    return launch_sort_scatter(pos, vel, ids, c->np, c->sort_key, c->sort_rank, c->slice_start,
-                               dst_pos, dst_vel, dst_ids, c->stream);
-  }));
-  c->sorted = true;
-  c->since_sort = 0;
-  return PM_OK;
-}
-
 pm_status copy_particles(pm_ctx* c, void* pos, float* vel, const void* src_pos,
                          const float* src_vel) {
   return timed(c, kcSortCopy, [&] {
@@ -792,14 +819,18 @@ static pm_status step_impl(pm_ctx* c, void* d_pos, float* d_vel, const double* t
     }
     gc.fd_units = drift(c->p, t0, t1) * fdu;
     // gather + kick + drift, fused with the deposit of the drifted particles
-    PM_TRY(timed(c, kcFill, [&] { return launch_fill_zero(c->mass, 8 * c->ncell + kStrayBytes, c->stream); }));
+    // (unsorted, a large deposit is binned on its own)
+    const bool split = !c->sorted && !en && c->np >= kBinMin;
+    if (!split)
+      PM_TRY(timed(c, kcFill, [&] { return launch_fill_zero(c->mass, 8 * c->ncell + kStrayBytes, c->stream); }));
     // once the particles have moved since the sort, a state whose adaptive
     // interval is short (strays are frequent) takes the wider windows
     const bool wide = sort_auto && c->sorted && c->wide_windows && c->since_sort > 0;
     PM_TRY(timed(c, kcGatherKD, [&] {
       return launch_gather(c->fixed, c->has_q && !psi, true, c->logn, cur_pos, cur_vel,
                            psi ? c->q : c->phi, c->q, c->np, gc,
-                           c->sorted ? &c->tmap : nullptr, c->mass, c->stream, Batch(), wide);
+                           c->sorted ? &c->tmap : nullptr, split ? nullptr : c->mass, c->stream,
+                           Batch(), wide);
     }));
     ++c->since_sort;
     if (en && (s > 0 || row0)) PM_TRY(energy_row(s));
@@ -809,10 +840,10 @@ static pm_status step_impl(pm_ctx* c, void* d_pos, float* d_vel, const double* t
     close = kick(c->p, tm, t1);
     if (s + 1 < nsteps && !en) {
       const Kick kn = merged(s + 1, close);
-      PM_TRY(run_fields(c, cur_pos, false, false, &kn));
+      PM_TRY(run_fields(c, cur_pos, false, split, &kn));
       psi = c->has_q;
     } else {
-      PM_TRY(run_fields(c, cur_pos, en, false));
+      PM_TRY(run_fields(c, cur_pos, en, split));
       psi = false;
     }
   }
@@ -909,15 +940,25 @@ pm_status pm_kinetic_split(pm_ctx* c, const void* d_pos, const float* d_vel, dou
   if (!c || !d_pos || !d_vel || !out) return PM_EINVAL;
   if (!(a > 0.0) || !isfinite(a)) return PM_EINVAL;
   if (!c->p.comoving && a != 1.0) return PM_EINVAL;
-  PM_TRY(run_deposit(c, d_pos));
+  // an unsorted context bins the particles once for the four deposits
+  const TileMap* tm = c->sorted ? &c->tmap : nullptr;
+  const void* pos = d_pos;
+  const float* vel = d_vel;
+  if (!tm && c->np >= kBinMin) {
+    PM_TRY(bin_into(c, c->bin_map, d_pos, d_vel, nullptr, c->pos_tmp, c->vel_tmp, nullptr));
+    tm = &c->bin_map;
+    pos = c->pos_tmp;
+    vel = c->vel_tmp;
+  }
+  PM_TRY(run_deposit(c, pos, tm));
   // delta and phi are adjacent 4 N^3-byte blocks: one FP64 mesh
   double* mom = reinterpret_cast<double*>(c->delta);
   const int nb = diag_node_blocks(c);
   for (int d = 0; d < 3; ++d) {
     PM_TRY(timed(c, kcFill, [&] { return launch_fill_zero(mom, 8 * c->ncell, c->stream); }));
     PM_TRY(timed(c, kcMomentum, [&] {
-      return launch_deposit_momentum(c->fixed, c->logn, d_pos, c->np, d_vel + d * c->np, mom,
-                                     c->sorted ? &c->tmap : nullptr, c->stream);
+      return launch_deposit_momentum(c->fixed, c->logn, pos, c->np, vel + d * c->np, mom, tm,
+                                     c->stream);
     }));
     PM_TRY(timed(c, kcDiagNodes, [&] {
       return launch_bulk_nodes(c->fixed, c->mass, mom, (int64_t)c->ncell, c->partials, nb,
@@ -952,7 +993,10 @@ pm_status pm_density_rms_diff(pm_ctx* c, const void* d_pos_a, const void* d_pos_
   // the reference state's mass mesh is kept in delta..phi (8 N^3 bytes)
   void* mass_b = c->delta;
   const size_t mesh_bytes = (c->fixed ? 8 : 4) * c->ncell;
-  PM_TRY(run_deposit(c, d_pos_b));
+  // on a sorted context the tile map can describe one of the two states at
+  // most: b is binned (read in the other state's order it took 1440 us at
+  // 256^3 and 245 at 128^3, binned 145 + 252 and 35 + 44)
+  PM_TRY(run_deposit(c, d_pos_b, c->sorted && c->np < kBinMin ? &c->tmap : nullptr));
   PM_TRY(dev(hipMemcpyAsync(mass_b, c->mass, mesh_bytes, hipMemcpyDeviceToDevice, c->stream)));
   PM_TRY(run_deposit(c, d_pos_a));
   const int nb = diag_node_blocks(c);
@@ -1370,8 +1414,8 @@ pm_status pm_batch_step(pm_batch* b, void* d_pos, float* d_vel, int32_t nactive,
     PM_TRY(dev(launch_fill_zero(c->tile_counts, cbytes, c->stream, bt)));
     PM_TRY(dev(launch_sort_count(c->fixed, d_pos, c->np, c->logn, c->tile_counts, c->sort_key,
                                  c->sort_rank, c->stream, bt)));
-    PM_TRY(dev(launch_sort_scan(c->tile_counts, c->tiles, c->scan_sums, c->slice_start, c->chunks,
-                                c->pieces, c->used, c->stream, bt)));
+    PM_TRY(dev(launch_sort_scan(c->tile_counts, c->tiles, c->scan_sums, c->slice_start, c->tmap,
+                                c->stream, bt)));
     PM_TRY(dev(launch_sort_scatter(d_pos, d_vel, nullptr, c->np, c->sort_key, c->sort_rank,
                                    c->slice_start, c->pos_tmp, c->vel_tmp, nullptr, c->stream,
                                    bt)));
@@ -1389,6 +1433,8 @@ pm_status pm_batch_step(pm_batch* b, void* d_pos, float* d_vel, int32_t nactive,
   // must know when each staging buffer's copy is done.
   auto enqueue = [&]() -> pm_status {
   if (!(flags & PM_CONTINUE)) {
+    // the sort due at the first step comes before the opening deposit
+    if (sort_every > 0) PM_TRY(sort_all());
     PM_TRY(dev(launch_fill_zero(c->mass, 8 * c->ncell + kStrayBytes, c->stream, bt)));
     if (c->fixed)
       PM_TRY(dev(sorted ? launch_deposit_fixed_tiled(static_cast<const uint32_t*>(d_pos), c->np,
@@ -1420,7 +1466,8 @@ pm_status pm_batch_step(pm_batch* b, void* d_pos, float* d_vel, int32_t nactive,
   gpsi.fd_units = 0.0;
   gpsi.psi = 1;
   for (int k = 0; k < nsteps; ++k) {
-    if (sort_every > 0 && k % sort_every == 0) PM_TRY(sort_all());
+    if (sort_every > 0 && k % sort_every == 0 && (k > 0 || (flags & PM_CONTINUE)))
+      PM_TRY(sort_all());
     PM_TRY(dev(launch_fill_zero(c->mass, 8 * c->ncell + kStrayBytes, c->stream, bt)));
     PM_TRY(dev(launch_gather(c->fixed, !psi, true, c->logn, d_pos, d_vel, psi ? c->q : c->phi,
                              c->q, c->np, psi ? gpsi : unused, sorted ? &c->tmap : nullptr,

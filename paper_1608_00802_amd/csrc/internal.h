@@ -199,16 +199,16 @@ hipError_t launch_deposit_fixed(const uint32_t* pos, int64_t np, int logn,
 hipError_t launch_deposit_f32(const float* pos, int64_t np, int logn, float* acc,
                               hipStream_t s, const Batch& bt = Batch());
 // Tiled variants.  The particle sort leaves the list of chunks: chunk k holds
-// the particles [y, z) of tile x (at most kChunk of them), *used chunks in all.
+// the particles [y, z) of tile x (at most kChunk of them).
 // The spline kernels, a hundred times the work per particle, take pieces in
 // the same form: a tile's particles in even shares of about kPiece, so that a
 // few dense tiles still fill the chip (10^6 particles in one object at 128^3
 // are 150 chunks but 490 pieces).
+// used[0] and used[1] are the lists' lengths.
 struct TileMap {
-  const uint4* chunks;
-  const unsigned* used;
-  const uint4* pieces;
-  const unsigned* used_pieces;
+  uint4* chunks;
+  uint4* pieces;
+  unsigned* used;
   int tiles;
 };
 constexpr unsigned kPiece = 2048;
@@ -252,12 +252,10 @@ hipError_t launch_deposit_f32_tiled(const float* pos, int64_t np, int logn, cons
 hipError_t launch_sort_count(bool fixed, const void* pos, int64_t np, int logn,
                              unsigned* counts, unsigned* key, unsigned* rank, hipStream_t s,
                              const Batch& bt = Batch());
-// slice_start: [tiles * kSlices + 1]; chunks, pieces: the TileMap's lists,
-// used[0], used[1] their lengths; sums: scratch of 3 * scan_blocks(tiles)
-// counters
+// slice_start: [tiles * kSlices + 1]; map receives the lists; sums: scratch of
+// 3 * scan_blocks(tiles) counters
 hipError_t launch_sort_scan(const unsigned* counts, int tiles, unsigned* sums,
-                            unsigned* slice_start, uint4* chunks, uint4* pieces,
-                            unsigned* used, hipStream_t s, const Batch& bt = Batch());
+                            unsigned* slice_start, const TileMap& map, hipStream_t s, const Batch& bt = Batch());
 hipError_t launch_sort_scatter(const void* pos, const float* vel, const int* ids, int64_t np,
                                const unsigned* key, const unsigned* rank,
                                const unsigned* slice_start, uint32_t* pos_out, float* vel_out,

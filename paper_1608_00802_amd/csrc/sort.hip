@@ -270,7 +270,7 @@ __global__ void __launch_bounds__(kScanBlock) k_sort_scan_down(const unsigned* _
   }
 }
 
-template <bool FIXED, bool IDS>
+template <bool VEL, bool IDS>
 __global__ void __launch_bounds__(kBlock) k_sort_scatter(
     const void* __restrict__ pos, const float* __restrict__ vel, const int* __restrict__ ids,
     int64_t np, const unsigned* __restrict__ key, const unsigned* __restrict__ rank,
@@ -292,7 +292,7 @@ __global__ void __launch_bounds__(kBlock) k_sort_scatter(
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       pos_out[d * np + dst] = static_cast<const uint32_t*>(pos)[d * np + i];
-      vel_out[d * np + dst] = vel[d * np + i];
+      if constexpr (VEL) vel_out[d * np + dst] = vel[d * np + i];
     }
     if constexpr (IDS) ids_out[dst] = ids[i];
   }
@@ -321,13 +321,12 @@ hipError_t launch_sort_count(bool fixed, const void* pos, int64_t np, int logn,
 }
 
 hipError_t launch_sort_scan(const unsigned* counts, int tiles, unsigned* sums,
-                            unsigned* slice_start, uint4* chunks, uint4* pieces,
-                            unsigned* used, hipStream_t s, const Batch& bt) {
+                            unsigned* slice_start, const TileMap& map, hipStream_t s, const Batch& bt) {
   const dim3 g(scan_blocks(tiles), bt.count);
   const int cs = count_stride(tiles);
   hipLaunchKernelGGL(k_sort_scan_reduce, g, dim3(kScanBlock), 0, s, counts, tiles, cs, sums, bt);
   hipLaunchKernelGGL(k_sort_scan_down, g, dim3(kScanBlock), 0, s, counts, tiles, cs, sums,
-                     slice_start, chunks, pieces, used, bt);
+                     slice_start, map.chunks, map.pieces, map.used, bt);
   return hipGetLastError();
 }
 
@@ -335,9 +334,13 @@ hipError_t launch_sort_scatter(const void* pos, const float* vel, const int* ids
                                const unsigned* key, const unsigned* rank, const unsigned* start,
                                uint32_t* pos_out, float* vel_out, int* ids_out,
                                hipStream_t s, const Batch& bt) {
-  // positions are moved as 32-bit words in both forms; ids only for single runs
+  // positions are moved as 32-bit words in both forms; ids only for single
+  // runs; without vel the positions alone
   const dim3 g(grid_p(np), bt.count);
-  if (ids && !bt.slots)
+  if (!vel)
+    hipLaunchKernelGGL((k_sort_scatter<false, false>), g, dim3(kBlock), 0, s, pos, vel, ids, np,
+                       key, rank, start, pos_out, vel_out, ids_out, bt);
+  else if (ids && !bt.slots)
     hipLaunchKernelGGL((k_sort_scatter<true, true>), g, dim3(kBlock), 0, s, pos, vel, ids, np,
                        key, rank, start, pos_out, vel_out, ids_out, bt);
   else

@@ -321,7 +321,7 @@ __global__ void __launch_bounds__(kSplineBlock, 4) k_spline_deposit_tiled(
   using Rc = Reach<H2>;
   using Tile = SplineTile<H2>;
   extern __shared__ unsigned long long win[];
-  const unsigned used = __builtin_amdgcn_readfirstlane(*tm.used_pieces);
+  const unsigned used = __builtin_amdgcn_readfirstlane(tm.used[1]);
   for (unsigned b = blockIdx.x; b < used; b += gridDim.x) {
     const uint4 pc = tm.pieces[b];
     const Tile tile(sp.logn, (int)__builtin_amdgcn_readfirstlane(pc.x));
@@ -493,7 +493,7 @@ __global__ void __launch_bounds__(kSplineBlock, H2 <= 7 && !STEP ? 8 : 5) k_spli
   using Tile = SplineTile<H2>;
   extern __shared__ float qwin[];
   float* pwin = qwin + spline_window<H2>(sp.logn);
-  const unsigned used = __builtin_amdgcn_readfirstlane(*tm.used_pieces);
+  const unsigned used = __builtin_amdgcn_readfirstlane(tm.used[1]);
   for (unsigned b = blockIdx.x; b < used; b += gridDim.x) {
     const uint4 pc = tm.pieces[b];
     const Tile tile(sp.logn, (int)__builtin_amdgcn_readfirstlane(pc.x));

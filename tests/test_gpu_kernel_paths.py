@@ -173,3 +173,68 @@ def test_spline_push_equals_separate_passes(pm, gpu, n, npart, h, prec):
     # a position word is one rounding of the drift on top
     d = (out[1][0] - out[0][0] + n / 2) % n - n / 2
     assert np.abs(d).max() <= 0.03 * (2.0 ** -16 * kick + 2.0 ** -22) + 2.0 ** -22 * n
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("n,npart,clumps", [(32, 1 << 17, False), (32, (1 << 17) + 1, True),
+                                            (64, 64 ** 3, True)])
+def test_binned_deposit_equals_direct(pm, gpu, n, npart, clumps, prec):
+    """From 2^17 particles on an unsorted deposit is binned: against the FP64
+    sum, and (fixed point) bitwise against halves below the limit deposited
+    directly; the second state of the density difference likewise."""
+    import torch
+    st = _state(n, npart, seed=npart, clumps=clumps)
+    ctx = pm.PMContext(pm.make_params(n, npart, float(n), precision=prec), device=gpu)
+    pos, vel = to_device(st, gpu, fp32_positions=prec == 0)
+    ctx.deposit(pos)
+    torch.cuda.synchronize()
+    op = oracle.Params(n=n, box=float(n), S=1.0, hbar_m=0.0)
+    if prec == 0:
+        acc = ctx.workspace[: 4 * n ** 3].view(torch.float32).cpu().numpy().astype(np.float64)
+        ref = oracle.deposit(pos.cpu().numpy().T.astype(np.float64), op).ravel() * npart / n ** 3
+        # as for the tiled deposit, and one half-ulp for each of the chunks of
+        # a tile past the first
+        assert np.all(np.abs(acc - ref) <= (11 + npart // 8192) * 2.0 ** -24 * ref + 1e-30)
+    else:
+        mass = ctx.workspace[: 8 * n ** 3].view(torch.int64).cpu().numpy().copy()
+        total = np.zeros(n ** 3, dtype=np.int64)
+        for part in np.array_split(np.arange(npart), 3):
+            sub = pm.PMContext(pm.make_params(n, len(part), float(n)), device=gpu)
+            sub.deposit(pos[:, part[0]: part[-1] + 1].contiguous())
+            torch.cuda.synchronize()
+            total += sub.workspace[: 8 * n ** 3].view(torch.int64).cpu().numpy()
+        assert np.array_equal(mass, total)
+    other, _ = to_device(_state(n, npart, seed=npart + 1, clumps=False), gpu,
+                         fp32_positions=prec == 0)
+    plain = ctx.density_rms_diff(pos, other)
+    ctx.sort(pos, vel)
+    again = ctx.density_rms_diff(pos, other)
+    assert again[1] == plain[1]
+    assert abs(again[0] - plain[0]) <= (0.0 if prec else 1e-3) * plain[0] + 1e-12 * plain[0]
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_unsorted_step_with_binned_deposit(pm, gpu, prec):
+    """A large unsorted call bins each step's deposit instead of adding from
+    the push: against the same state sorted, which never does."""
+    import torch
+    n, npart = 32, (1 << 17) + 77
+    st = _state(n, npart, seed=5, clumps=False)
+    out = []
+    for tiled in (False, True):
+        ctx = pm.PMContext(pm.make_params(n, npart, float(n), hbar_over_m=0.01, precision=prec),
+                           device=gpu)
+        pos, vel = to_device(st, gpu, fp32_positions=prec == 0)
+        ids = torch.arange(npart, dtype=torch.int32, device=gpu)
+        if tiled:
+            ctx.sort(pos, vel, ids)
+        ctx.step(pos, vel, [0.0, 0.05, 0.1, 0.15])
+        torch.cuda.synchronize()
+        p, v = torch.empty_like(pos), torch.empty_like(vel)
+        p[:, ids.long()], v[:, ids.long()] = pos, vel
+        out.append((p, v))
+    if prec:
+        assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    else:   # float sums of the density differ in order: 2^-20 of it in the force
+        kick = float((out[1][1] - torch.from_numpy(st.vel32.copy()).to(gpu)).abs().max())
+        assert float((out[0][1] - out[1][1]).abs().max()) <= 1e-3 * kick
