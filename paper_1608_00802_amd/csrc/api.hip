@@ -21,13 +21,13 @@ namespace {
 enum KernelClass : int {
   kcFill, kcDeposit, kcR2C, kcFftY, kcFftX, kcFftYInv, kcC2R, kcQpot, kcGatherKD, kcKick,
   kcForce, kcReduce, kcKinetic, kcSortCount, kcSortScan, kcSortScatter, kcSortCopy,
-  kcMomentum, kcDiagNodes, kcPower, kcSpline, kcSplineForce, kcEnergyRow, kcCount
+  kcMomentum, kcDiagNodes, kcPower, kcSpline, kcSplineForce, kcEnergyRow, kcCombine, kcCount
 };
 const char* const kKernelNames[kcCount] = {
     "fill_zero", "deposit", "r2c_z", "fft_y", "fft_x_green", "fft_y_inv", "c2r_z",
     "qpot", "gather_kick_drift", "kick", "force", "reduce", "kinetic", "sort_count",
     "sort_scan", "sort_scatter", "sort_copy", "momentum_deposit", "diag_nodes", "fft_x_power", "spline_deposit",
-    "spline_qforce", "energy_row"};
+    "spline_qforce", "energy_row", "combine"};
 
 struct Timer {
   bool on = false;
@@ -434,6 +434,25 @@ pm_status run_fields(pm_ctx* c, const void* pos, bool energy, bool deposit = tru
   return PM_OK;
 }
 
+// Unsorted, the push and the force read a particle's 32 nodes from the mesh;
+// one pass over the cells that forms fg phi + fq Q first (in the spectrum's
+// place, free between solves, which is larger than a mesh) halves those reads.
+// pm_force calls: 256^3 in lattice order 514 -> 310 us, in clumps 1022 -> 527;
+// 600001 random particles at 128^3 394 -> 97; 64^3 15 -> 11; 32^3, where the
+// extra launch shows, 5.6 against 8.4.  With far fewer particles than cells
+// the pass (12 bytes per cell) costs more than particles in order gain.
+constexpr int64_t kCombineMin = 1 << 16;
+bool combine_pays(const pm_ctx* c) {
+  return c->np >= kCombineMin && c->np >= (int64_t)(c->ncell / 8);
+}
+bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
+float* combined(pm_ctx* c) { return reinterpret_cast<float*>(c->spec); }
+pm_status run_combine(pm_ctx* c, const float* phi, const float* q, float fg, float fq) {
+  return timed(c, kcCombine, [&] {
+    return launch_combine(phi, q, combined(c), c->ncell, fg, fq, c->stream);
+  });
+}
+
 pm_status copy_out(pm_ctx* c, float* dst, const float* src) {
   if (!dst || dst == src) return PM_OK;
   return dev(hipMemcpyAsync(dst, src, 4 * c->ncell, hipMemcpyDeviceToDevice, c->stream));
@@ -622,9 +641,16 @@ pm_status pm_force(pm_ctx* c, const float* d_phi, const float* d_q, const void* 
   if (!d_phi && !c->have_phi) return PM_ESTATE;
   const bool use_q = d_q != nullptr || (c->has_q && c->have_q);
   if (!d_q && c->has_q && !c->have_q) return PM_ESTATE;
+  float fg = (float)(1.0 / a), fq = (float)(1.0 / (a * a));
+  const bool one = use_q && combine_pays(c) && aligned16(phi) && aligned16(q);
+  if (one) {
+    PM_TRY(run_combine(c, phi, q, fg, fq));
+    phi = combined(c);
+    fg = 1.0f;
+  }
   return timed(c, kcForce, [&] {
-    return launch_force(c->fixed, use_q, c->logn, d_pos, phi, q, c->np, (float)(1.0 / a),
-                        (float)(1.0 / (a * a)), d_acc, c->stream);
+    return launch_force(c->fixed, use_q && !one, c->logn, d_pos, phi, q, c->np, fg, fq, d_acc,
+                        c->stream);
   });
 }
 
@@ -855,8 +881,14 @@ static pm_status step_impl(pm_ctx* c, void* d_pos, float* d_vel, const double* t
   // closing half-kick; if the particles ended in the workspace copies, the
   // same pass writes them back to the caller's arrays
   const bool back = cur_pos != d_pos;
+  const bool one = c->has_q && !c->sorted && !en && combine_pays(c);
+  if (one) {
+    PM_TRY(run_combine(c, c->phi, c->q, gc.fg, gc.fq));
+    gc.fg = 1.0f;
+  }
   PM_TRY(timed(c, kcKick, [&] {
-    return launch_gather(c->fixed, c->has_q, false, c->logn, cur_pos, cur_vel, c->phi, c->q,
+    return launch_gather(c->fixed, c->has_q && !one, false, c->logn, cur_pos, cur_vel,
+                         one ? combined(c) : c->phi, c->q,
                          c->np, gc, c->sorted ? &c->tmap : nullptr, nullptr, c->stream, Batch(),
                          false, back ? d_pos : nullptr, back ? d_vel : nullptr);
   }));

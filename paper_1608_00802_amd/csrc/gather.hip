@@ -674,6 +674,29 @@ hipError_t preload_wide(int logn) {
   return e;
 }
 
+// F = fg phi + fq Q over the mesh, with mesh_f's rounding.
+__global__ void __launch_bounds__(kBlock) k_combine(const float4* __restrict__ phi,
+                                                    const float4* __restrict__ q,
+                                                    float4* __restrict__ out, size_t n4, float fg,
+                                                    float fq) {
+  const size_t stride = (size_t)gridDim.x * kBlock;
+  for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n4; i += stride) {
+    const float4 a = phi[i], b = q[i];
+    out[i] = make_float4(fmaf(fq, b.x, fg * a.x), fmaf(fq, b.y, fg * a.y),
+                         fmaf(fq, b.z, fg * a.z), fmaf(fq, b.w, fg * a.w));
+  }
+}
+
+hipError_t launch_combine(const float* phi, const float* q, float* out, size_t ncell, float fg,
+                          float fq, hipStream_t s) {
+  const size_t n4 = ncell / 4;
+  const size_t b = (n4 + kBlock - 1) / kBlock;
+  hipLaunchKernelGGL(k_combine, dim3((unsigned)(b < 8192 ? b : 8192)), dim3(kBlock), 0, s,
+                     reinterpret_cast<const float4*>(phi), reinterpret_cast<const float4*>(q),
+                     reinterpret_cast<float4*>(out), n4, fg, fq);
+  return hipGetLastError();
+}
+
 hipError_t launch_force(bool fixed, bool has_q, int logn, const void* pos, const float* phi,
                         const float* q, int64_t np, float fg, float fq, float* acc,
                         hipStream_t s) {

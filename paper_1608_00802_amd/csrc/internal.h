@@ -300,6 +300,9 @@ hipError_t launch_gather(bool fixed, bool has_q, bool drift, int logn, void* pos
                          const GatherConst& gc, const TileMap* tm, void* deposit_mass,
                          hipStream_t s, const Batch& bt = Batch(), bool wide = false,
                          void* pos_out = nullptr, float* vel_out = nullptr);
+// out = fg phi + fq q over ncell nodes (a multiple of 4; 16-byte aligned).
+hipError_t launch_combine(const float* phi, const float* q, float* out, size_t ncell, float fg,
+                          float fq, hipStream_t s);
 hipError_t preload_wide(int logn);
 hipError_t launch_force(bool fixed, bool has_q, int logn, const void* pos,
                         const float* phi, const float* q, int64_t np, float fg, float fq,

@@ -238,3 +238,27 @@ def test_unsorted_step_with_binned_deposit(pm, gpu, prec):
     else:   # float sums of the density differ in order: 2^-20 of it in the force
         kick = float((out[1][1] - torch.from_numpy(st.vel32.copy()).to(gpu)).abs().max())
         assert float((out[0][1] - out[1][1]).abs().max()) <= 1e-3 * kick
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_force_of_combined_potential(pm, gpu, prec):
+    """From 2^16 particles on the force reads fg phi + fq Q formed beforehand:
+    bitwise the force of parts of the particles that are below the limit."""
+    import torch
+    n, npart = 32, (1 << 16) + 5
+    pos, _ = to_device(_state(n, npart, seed=9), gpu, fp32_positions=prec == 0)
+    gen = torch.Generator(device=gpu).manual_seed(1)
+    phi, q = (torch.randn(n ** 3, generator=gen, device=gpu) for _ in range(2))
+
+    def force(p):
+        lp = pm.make_params(n, p.shape[1], float(n), hbar_over_m=1.0, comoving=True,
+                            precision=prec)
+        acc = torch.empty(p.shape, dtype=torch.float32, device=gpu)
+        ctx = pm.PMContext(lp, device=gpu)
+        ctx.force(p, acc, 0.3, phi, q)
+        torch.cuda.synchronize()
+        return acc
+
+    whole = force(pos)
+    parts = torch.cat([force(p.contiguous()) for p in pos.split(30000, dim=1)], dim=1)
+    assert torch.equal(whole, parts)
