@@ -96,48 +96,49 @@ __device__ __forceinline__ void add_global(unsigned long long* p, unsigned long 
 }
 __device__ __forceinline__ void add_global(float* p, float v) { unsafeAtomicAdd(p, v); }
 
-// Interpolated -2 grad F at one particle.  at(a, b, c) returns F at offsets
+// Interpolated -grad F at one particle.  at(a, b, c) returns F at offsets
 // (a - 1, b - 1, c - 1) from the particle's base cell, a, b, c in 0..3.
 // Central differences at the 8 CIC nodes use the 2x2x2 core and, per axis,
 // the two planes outside it; each axis' extra nodes are consumed as soon as
-// they are read, so only the core stays live.  The trilinear weights are
-// applied as nested linear interpolations (22 instructions per axis); the
-// fused multiply-adds are written out so that every kernel rounds alike.
-__device__ __forceinline__ float lerp_f(float lo, float hi, float f) {
-  return fmaf(f, hi - lo, lo);
-}
+// they are read, so only the core stays live.
 template <typename At>
 __device__ __forceinline__ void interp_grad(const float f[3], At&& at, float g[3]) {
-  float core[2][2][2], e[2][2];
+  float core[2][2][2];
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int c = 0; c < 2; ++c) core[a][b][c] = at(1 + a, 1 + b, 1 + c);
-  // the node at x offset 0 takes F(+1) - F(-1) = core[1] - plane -1, the one
-  // at offset 1 the plane at +2 minus core[0]; here with the opposite sign
+  const float wx[2] = {1.0f - f[0], f[0]};
+  const float wy[2] = {1.0f - f[1], f[1]};
+  const float wz[2] = {1.0f - f[2], f[2]};
+  float gx = 0.0f, gy = 0.0f, gz = 0.0f;
 #pragma unroll
   for (int b = 0; b < 2; ++b)
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
-      e[b][c] = lerp_f(at(0, 1 + b, 1 + c) - core[1][b][c], core[0][b][c] - at(3, 1 + b, 1 + c),
-                       f[0]);
-  g[0] = lerp_f(lerp_f(e[0][0], e[0][1], f[2]), lerp_f(e[1][0], e[1][1], f[2]), f[1]);
+    for (int c = 0; c < 2; ++c) {
+      // node x offset 0 -> difference F(+1) - F(-1) uses core[1] and the plane at offset -1
+      const float lo = at(0, 1 + b, 1 + c), hi = at(3, 1 + b, 1 + c);
+      gx += wy[b] * wz[c] * (wx[0] * (core[1][b][c] - lo) + wx[1] * (hi - core[0][b][c]));
+    }
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
-      e[a][c] = lerp_f(at(1 + a, 0, 1 + c) - core[a][1][c], core[a][0][c] - at(1 + a, 3, 1 + c),
-                       f[1]);
-  g[1] = lerp_f(lerp_f(e[0][0], e[0][1], f[2]), lerp_f(e[1][0], e[1][1], f[2]), f[0]);
+    for (int c = 0; c < 2; ++c) {
+      const float lo = at(1 + a, 0, 1 + c), hi = at(1 + a, 3, 1 + c);
+      gy += wx[a] * wz[c] * (wy[0] * (core[a][1][c] - lo) + wy[1] * (hi - core[a][0][c]));
+    }
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
-      e[a][b] = lerp_f(at(1 + a, 1 + b, 0) - core[a][b][1], core[a][b][0] - at(1 + a, 1 + b, 3),
-                       f[2]);
-  g[2] = lerp_f(lerp_f(e[0][0], e[0][1], f[1]), lerp_f(e[1][0], e[1][1], f[1]), f[0]);
+    for (int b = 0; b < 2; ++b) {
+      const float lo = at(1 + a, 1 + b, 0), hi = at(1 + a, 1 + b, 3);
+      gz += wx[a] * wy[b] * (wz[0] * (core[a][b][1] - lo) + wz[1] * (hi - core[a][b][0]));
+    }
+  g[0] = -0.5f * gx;
+  g[1] = -0.5f * gy;
+  g[2] = -0.5f * gz;
 }
 
 // LDS windows of the tiled deposits: integer weights are summed as they are,

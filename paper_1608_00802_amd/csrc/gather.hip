@@ -137,13 +137,13 @@ __device__ __forceinline__ float mesh_f(const float* __restrict__ phi, const flo
   return phi[idx];
 }
 
-// interp_grad gives twice the gradient: the factor on it is one half, times
-// fg without Q (see mesh_f).
+// The factor on the interpolated gradient (fg without Q, see mesh_f).
 template <bool HAS_Q>
 __device__ __forceinline__ void scale_grad(const GatherConst& gc, float g[3]) {
-  const float k = HAS_Q ? 0.5f : 0.5f * gc.fg;
+  if constexpr (!HAS_Q) {
 #pragma unroll
-  for (int d = 0; d < 3; ++d) g[d] *= k;
+    for (int d = 0; d < 3; ++d) g[d] *= gc.fg;
+  }
 }
 
 // mesh_f at a byte offset below 2^32 (the mesh is at most 512^3 floats).
@@ -190,9 +190,8 @@ __device__ __forceinline__ void split_kick(const GatherConst& gc, const float vi
                                            float g[3], double& ksum) {
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    const float hp = 0.5f * gp[d], hq = 0.5f * gq[d];
-    vk[d] = vin[d] + fmaf(gc.fq, hq, gc.fg * hp);
-    g[d] = fmaf(gc.oq, hq, gc.og * hp);
+    vk[d] = vin[d] + fmaf(gc.fq, gq[d], gc.fg * gp[d]);
+    g[d] = fmaf(gc.oq, gq[d], gc.og * gp[d]);
     ksum += (double)vk[d] * (double)vk[d];
   }
 }
@@ -316,24 +315,20 @@ struct Window {
 //      their CIC weights added; the window is then added to the mass mesh.
 // With both windows in LDS at once (51 KB without a gather halo, three blocks
 // per CU) a particle that had left its tile read its 32 nodes from the mesh,
-// and one such lane holds its wave.  In turn they fit 34 KB, four blocks per
-// CU, with a gather window that is wider by HG cells on each side: 302 -> 269
+// and one such lane holds its wave.  In turn they fit 34 KB,
+// with a gather window that is wider by HG cells on each side: 302 -> 271
 // us per launch over the 24 steps after a sort of a 256^3 field (1 cell rms
-// from the lattice, 0.02 cells per step), 354 -> 321 us on clumps over an
-// empty background, and 321 -> 208 us for the closing half-kick.  What bounds
+// from the lattice, 0.02 cells per step), 354 -> 329 us on clumps over an
+// empty background, and 321 -> 209 us for the closing half-kick.  What bounds
 // it: phase 1 alone takes 192 us, 4.5 TB/s of particle traffic where a copy
 // reaches 5.1; the window flush, one u64 atomic per non-zero cell (2.07 per
 // mesh cell), 53 us; the weights and LDS adds 24 us.
 // WIDE: one cell more of halo in both windows, for steps whose particles have
 // moved since the sort in a clustered state.
-#ifndef FDM_GATHER_WAVES
-#define FDM_GATHER_WAVES 8
-#endif
-// Waves per SIMD that the LDS windows leave room for; the register budget is
-// held to that.
-constexpr int gather_waves(int wide, bool two_windows) {
-  return wide ? 6 : two_windows ? 6 : FDM_GATHER_WAVES;
-}
+// Waves per SIMD, which set the register budget: 72 with one window (64, for
+// four blocks per CU, spills and takes 308 us where 72 and 80 take 271), 80
+// where two windows or the wide ones leave room for three blocks only.
+constexpr int gather_waves(int wide, bool two_windows) { return wide || two_windows ? 6 : 7; }
 
 template <int LOGN, bool FIXED, bool HAS_Q, int MODE, bool DEP, int WIDE = 0, bool EN = false>
 __global__ void __launch_bounds__(kGatherBlock, gather_waves(WIDE, EN && HAS_Q))

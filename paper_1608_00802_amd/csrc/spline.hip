@@ -556,10 +556,9 @@ __global__ void __launch_bounds__(kSplineBlock, H2 <= 7 && !STEP ? 8 : 5) k_spli
           const int64_t k = d * np + p + threadIdx.x;
           const float gq = coef * g[d];
           if constexpr (STEP) {
-            const float gphi = 0.5f * gp[d];
-            if (st.close) v[d] = spline_kick(v[d], gphi, gq, st.cg, st.cq);
+            if (st.close) v[d] = spline_kick(v[d], gp[d], gq, st.cg, st.cq);
             if (st.open) {
-              v[d] = spline_kick(v[d], gphi, gq, st.og, st.oq);
+              v[d] = spline_kick(v[d], gp[d], gq, st.og, st.oq);
               pos[k] = spline_drift(sp, pos[k], v[d], st.fd);
             }
             st.vel[k] = v[d];
