@@ -21,13 +21,14 @@ namespace {
 enum KernelClass : int {
   kcFill, kcDeposit, kcR2C, kcFftY, kcFftX, kcFftYInv, kcC2R, kcQpot, kcGatherKD, kcKick,
   kcForce, kcReduce, kcKinetic, kcSortCount, kcSortScan, kcSortScatter, kcSortCopy,
-  kcMomentum, kcDiagNodes, kcPower, kcSpline, kcSplineForce, kcEnergyRow, kcCombine, kcCount
+  kcMomentum, kcDiagNodes, kcPower, kcSpline, kcSplineForce, kcEnergyRow, kcCombine, kcC2RQ,
+  kcCount
 };
 const char* const kKernelNames[kcCount] = {
     "fill_zero", "deposit", "r2c_z", "fft_y", "fft_x_green", "fft_y_inv", "c2r_z",
     "qpot", "gather_kick_drift", "kick", "force", "reduce", "kinetic", "sort_count",
     "sort_scan", "sort_scatter", "sort_copy", "momentum_deposit", "diag_nodes", "fft_x_power", "spline_deposit",
-    "spline_qforce", "energy_row", "combine"};
+    "spline_qforce", "energy_row", "combine", "c2r_q"};
 
 struct Timer {
   bool on = false;
@@ -389,7 +390,7 @@ pm_status run_deposit(pm_ctx* c, const void* pos) {
 
 // Forward z-pass from the context's mass mesh (or from a given delta),
 // remaining passes, potential into c->phi.
-pm_status run_poisson(pm_ctx* c, int src, const void* in) {
+pm_status run_to_last_pass(pm_ctx* c, int src, const void* in) {
   PM_TRY(timed(c, kcR2C, [&] {
     return launch_r2c_z(c->logn, src, in, c->delta, c->spec, c->tw, c->conv, c->stream);
   }));
@@ -399,21 +400,33 @@ pm_status run_poisson(pm_ctx* c, int src, const void* in) {
   PM_TRY(timed(c, kcFftX, [&] {
     return launch_fft_x_green(c->logn, c->spec, c->tw, c->s2, gscale, c->stream);
   }));
-  PM_TRY(timed(c, kcFftYInv, [&] { return launch_fft_y(c->logn, c->spec, c->tw, true, c->stream); }));
+  return timed(c, kcFftYInv, [&] { return launch_fft_y(c->logn, c->spec, c->tw, true, c->stream); });
+}
+pm_status run_poisson(pm_ctx* c, int src, const void* in) {
+  PM_TRY(run_to_last_pass(c, src, in));
   return timed(c, kcC2R, [&] { return launch_c2r_z(c->logn, c->spec, c->tw, c->phi, c->stream); });
 }
-
-pm_status run_qpot(pm_ctx* c, const float* delta, bool use_mass, int out,
-                   const Kick* psi = nullptr) {
+// The potential and Q (or psi, without phi; or Q with the energy partials)
+// from the mass mesh: the stencil runs in the last pass of the solve.
+pm_status run_poisson_q(pm_ctx* c, int src, int out, const Kick* psi = nullptr) {
+  PM_TRY(run_to_last_pass(c, src, c->mass));
   QConst qc = c->qc;
-  if (!use_mass) qc.fp64_below = -1.0;
   if (psi) {
     qc.psi_g = (float)psi->g;
     qc.psi_q = (float)psi->q;
   }
+  return timed(c, kcC2RQ, [&] {
+    return launch_c2r_q(c->logn, c->fixed, out, c->spec, c->tw, c->delta, c->mass, c->phi, c->q,
+                        qc, c->partials, c->stream);
+  });
+}
+
+pm_status run_qpot(pm_ctx* c, const float* delta, bool use_mass) {
+  QConst qc = c->qc;
+  if (!use_mass) qc.fp64_below = -1.0;
   return timed(c, kcQpot, [&] {
-    return launch_qpot(c->logn, c->fixed, out, delta, static_cast<const long long*>(c->mass),
-                       c->phi, c->q, qc, c->partials, c->stream);
+    return launch_qpot(c->logn, c->fixed, delta, static_cast<const long long*>(c->mass), c->q, qc,
+                       c->stream);
   });
 }
 
@@ -424,12 +437,15 @@ pm_status run_qpot(pm_ctx* c, const float* delta, bool use_mass, int out,
 pm_status run_fields(pm_ctx* c, const void* pos, bool energy, bool deposit = true,
                      const Kick* psi = nullptr) {
   if (deposit) PM_TRY(run_deposit(c, pos));
-  PM_TRY(run_poisson(c, c->fixed ? kSrcMass64 : kSrcAcc32, c->mass));
-  c->have_delta = true;
-  c->have_phi = true;
+  const int src = c->fixed ? kSrcMass64 : kSrcAcc32;
   const bool to_psi = psi && c->has_q && !energy;
   if (c->has_q || energy)
-    PM_TRY(run_qpot(c, c->delta, true, energy ? kOutEnergy : to_psi ? kOutPsi : kOutQ, psi));
+    PM_TRY(run_poisson_q(c, src, energy ? kOutEnergy : to_psi ? kOutPsi : kOutQ,
+                         to_psi ? psi : nullptr));
+  else
+    PM_TRY(run_poisson(c, src, c->mass));
+  c->have_delta = true;
+  c->have_phi = !to_psi;
   c->have_q = c->has_q && !to_psi;
   return PM_OK;
 }
@@ -540,7 +556,7 @@ pm_status ctx_setup(pm_ctx* c, const pm_params* params, char* base, hipStream_t 
   c->tmap = tile_map(L.chunks, L.pieces, L.used);
   c->bin_map = tile_map(L.bin_chunks, L.bin_pieces, L.bin_used);
   c->sorted = false;
-  c->q_blocks = qpot_blocks(c->logn);
+  c->q_blocks = c2r_q_blocks(c->logn);
   c->k_blocks = kinetic_blocks(c->np);
   // constant tables, built in FP64 and rounded once
   std::vector<float2> tw(c->N);
@@ -621,10 +637,10 @@ pm_status pm_poisson(pm_ctx* c, const float* d_delta, float* d_phi) {
 pm_status pm_qpot(pm_ctx* c, const float* d_delta, float* d_q) {
   if (!c) return PM_EINVAL;
   if (d_delta) {
-    PM_TRY(run_qpot(c, d_delta, false, kOutQ));
+    PM_TRY(run_qpot(c, d_delta, false));
   } else {
     if (!c->have_delta) return PM_ESTATE;
-    PM_TRY(run_qpot(c, c->delta, c->fixed, kOutQ));
+    PM_TRY(run_qpot(c, c->delta, c->fixed));
   }
   c->have_q = true;
   c->fields_at_pos = false;
@@ -1148,8 +1164,7 @@ pm_status pm_spline_step(pm_ctx* c, void* d_pos, float* d_vel, const double* tim
   const bool fused = c->sorted && c->has_q && spline_step_fused((float)h);
   auto fields = [&]() -> pm_status {
     PM_TRY(run_spline_density(c, d_pos, h));
-    PM_TRY(run_poisson(c, kSrcMass64, c->mass));
-    return c->has_q ? run_qpot(c, c->delta, c->fixed, kOutQ) : PM_OK;
+    return c->has_q ? run_poisson_q(c, kSrcMass64, kOutQ) : run_poisson(c, kSrcMass64, c->mass);
   };
   auto forces = [&]() -> pm_status {
     PM_TRY(timed(c, kcForce, [&] {
@@ -1220,8 +1235,7 @@ pm_status pm_spline_energy(pm_ctx* c, const void* d_pos, const float* d_vel, dou
   if (!(a > 0.0) || !isfinite(a)) return PM_EINVAL;
   if (!c->p.comoving && a != 1.0) return PM_EINVAL;
   PM_TRY(run_spline_density(c, d_pos, h));
-  PM_TRY(run_poisson(c, kSrcMass64, c->mass));
-  PM_TRY(run_qpot(c, c->delta, c->fixed, kOutEnergy));
+  PM_TRY(run_poisson_q(c, kSrcMass64, kOutEnergy));
   PM_TRY(timed(c, kcReduce, [&] {
     return launch_reduce(c->partials, c->q_blocks, 2, c->result, c->stream);
   }));
@@ -1436,10 +1450,8 @@ pm_status pm_batch_step(pm_batch* b, void* d_pos, float* d_vel, int32_t nactive,
     PM_TRY(dev(launch_fft_y(c->logn, c->spec, c->tw, false, c->stream, bt)));
     PM_TRY(dev(launch_fft_x_green(c->logn, c->spec, c->tw, c->s2, gscale, c->stream, bt)));
     PM_TRY(dev(launch_fft_y(c->logn, c->spec, c->tw, true, c->stream, bt)));
-    PM_TRY(dev(launch_c2r_z(c->logn, c->spec, c->tw, c->phi, c->stream, bt)));
-    return dev(launch_qpot(c->logn, c->fixed, to_psi ? kOutPsi : kOutQ, c->delta,
-                           static_cast<const long long*>(c->mass), c->phi, c->q, c->qc,
-                           c->partials, c->stream, bq));
+    return dev(launch_c2r_q(c->logn, c->fixed, to_psi ? kOutPsi : kOutQ, c->spec, c->tw, c->delta,
+                            c->mass, c->phi, c->q, c->qc, c->partials, c->stream, bq));
   };
   auto sort_all = [&]() -> pm_status {
     const size_t cbytes = 4 * (size_t)kSlices * count_stride(c->tiles);

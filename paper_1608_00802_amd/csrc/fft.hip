@@ -27,6 +27,7 @@
 // stage, natural order at the end.  Twiddles come from an FP64-built table
 // exp(-2 pi i k / N) staged in LDS.
 #include "internal.h"
+#include "qpot.h"
 
 namespace fdm {
 
@@ -527,47 +528,38 @@ __global__ void __launch_bounds__(RegTiles<1 << LOGN>::XT) k_fft_x_green_reg(flo
 }
 
 // ---------------------------------------------------------------- pass 5
-template <int LOGN>
-__global__ void __launch_bounds__(kZBlock) k_c2r_z(const float2* __restrict__ spec,
-                                                  const float2* __restrict__ tw,
-                                                  float* __restrict__ out, Batch bt) {
-  {
-    const int sl = bslot(bt);
-    spec = woff(spec, bt, sl);
-    out = woff(out, bt, sl);
-  }
+// The rows y0 .. y0 + TZ of plane x, inverse transformed into buf (rows of
+// H + 1 entries) by NT threads.
+template <int LOGN, int TZ, int NT>
+__device__ __forceinline__ void c2r_rows(const float2* __restrict__ spec,
+                                         const float2* __restrict__ tw, int x, int y0,
+                                         float2* buf, float2* tws) {
   constexpr int N = 1 << LOGN;
   constexpr int H = N / 2;
-  constexpr int TZ = Tiles<N>::TZ;
   constexpr int LP = H + 1;
-  __shared__ float2 buf[TZ * LP];
-  __shared__ float2 tws[N];
   const int tid = threadIdx.x;
-  const int zb = (int)xcd_block(blockIdx.x, gridDim.x, Tiles<N>::XG);
-  const int x = zb / (N / TZ);
-  const int y0 = (zb % (N / TZ)) * TZ;
-  for (int k = tid; k < N; k += kZBlock) tws[k] = tw[k];
+  for (int k = tid; k < N; k += NT) tws[k] = tw[k];
   {
     // all of a thread's loads are issued before the first is used
     constexpr int NE = (H + 1) * TZ;
-    constexpr int PER = (NE + kZBlock - 1) / kZBlock;
+    constexpr int PER = (NE + NT - 1) / NT;
     float2 v[PER];
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-      const int idx = tid + k * kZBlock;
-      if (NE % kZBlock == 0 || idx < NE)
+      const int idx = tid + k * NT;
+      if (NE % NT == 0 || idx < NE)
         v[k] = spec[((size_t)(idx / TZ) * N + x) * N + y0 + idx % TZ];
     }
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-      const int idx = tid + k * kZBlock;
-      if (NE % kZBlock == 0 || idx < NE) buf[(idx % TZ) * LP + idx / TZ] = v[k];
+      const int idx = tid + k * NT;
+      if (NE % NT == 0 || idx < NE) buf[(idx % TZ) * LP + idx / TZ] = v[k];
     }
   }
   __syncthreads();
   // pack: E = (X_k + conj X_{H-k})/2, O = (X_k - conj X_{H-k}) conj(w^k)/2,
   // Z_k = E + i O, Z_{H-k} = conj(E) + i conj(O)
-  for (int idx = tid; idx < TZ * (H / 2 + 1); idx += kZBlock) {
+  for (int idx = tid; idx < TZ * (H / 2 + 1); idx += NT) {
     const int r = idx / (H / 2 + 1), k = idx % (H / 2 + 1);
     const float2 xk = buf[r * LP + k];
     const float2 xm = cconj(buf[r * LP + H - k]);
@@ -577,10 +569,201 @@ __global__ void __launch_bounds__(kZBlock) k_c2r_z(const float2* __restrict__ sp
     if (k != 0 && k != H / 2) buf[r * LP + H - k] = make_float2(e.x + o.y, -e.y + o.x);
   }
   __syncthreads();
-  fft_rows<H, TZ, kZBlock, 2, true>(buf, tws);
+  fft_rows<H, TZ, NT, 2, true>(buf, tws);
+}
+
+template <int LOGN>
+__global__ void __launch_bounds__(kZBlock) k_c2r_z(const float2* __restrict__ spec,
+                                                  const float2* __restrict__ tw,
+                                                  float* __restrict__ out, Batch bt) {
+  {
+    const int sl = bslot(bt);
+    spec = woff(spec, bt, sl);
+    out = woff(out, bt, sl);
+  }
+  constexpr int N = 1 << LOGN, H = N / 2, LP = H + 1, TZ = Tiles<N>::TZ;
+  __shared__ float2 buf[TZ * LP];
+  __shared__ float2 tws[N];
+  const int tid = threadIdx.x;
+  const int zb = (int)xcd_block(blockIdx.x, gridDim.x, Tiles<N>::XG);
+  const int x = zb / (N / TZ);
+  const int y0 = (zb % (N / TZ)) * TZ;
+  c2r_rows<LOGN, TZ, kZBlock>(spec, tw, x, y0, buf, tws);
   for (int idx = tid; idx < TZ * H; idx += kZBlock) {
     const int r = idx / H, n = idx % H;
     *reinterpret_cast<float2*>(out + ((size_t)x * N + y0 + r) * N + 2 * n) = buf[r * LP + n];
+  }
+}
+
+// Rows and threads per block of the pass with the stencil: 16 rows up to
+// 64^3, one pair of cells per thread, so that one run's blocks spread over the
+// CUs (64^3: 256 blocks of 16 rows instead of 64 of a plane each).
+template <int N>
+struct QTiles {
+  static constexpr int TZ = N <= 64 ? 16 : Tiles<N>::TZ;
+  static constexpr int NT = N <= 64 ? 8 * N : kZBlock;
+};
+
+// Pass 5 and the Q stencil in one: phi of the block's rows stays in registers
+// while their s-values and those of the rows next to them take its place in
+// LDS; the x-neighbours' come from memory.  psi then needs no phi in memory
+// (OUT = kOutPsi writes psi alone; kOutQ and kOutEnergy write phi and Q).
+// The sums are those of the stencil kernels, in their order.
+// Bound by memory: 201 MB at 256^3 (spectrum and delta in, psi out; a block's
+// x-neighbours run on its XCD, the block index being a multiple of 8 apart,
+// and find their rows in its L2) take 49.6 us, 4.1 TB/s, where the pass and
+// the stencil took 30.7 and 49.5 with phi in memory between them; 512^3 515
+// against 575 us. Near-empty cells take six more square roots each in FP64:
+// 102.7 against 106.6 us on 256^3 clumps over a near-empty background.
+template <int LOGN, bool FIXED, int OUT>
+__global__ void __launch_bounds__(QTiles<1 << LOGN>::NT) k_c2r_q(const float2* __restrict__ spec,
+                                                  const float2* __restrict__ tw,
+                                                  const float* __restrict__ delta,
+                                                  const long long* __restrict__ mass,
+                                                  float* __restrict__ phi, float* __restrict__ q,
+                                                  QConst qc, double* __restrict__ partials,
+                                                  Batch bt) {
+  {
+    const int sl = bslot(bt);
+    spec = woff(spec, bt, sl);
+    delta = woff(delta, bt, sl);
+    mass = woff(mass, bt, sl);
+    phi = woff(phi, bt, sl);
+    q = woff(q, bt, sl);
+    partials = woff(partials, bt, sl);
+    if (bt.consts) {
+      qc.coef = bt.consts[blockIdx.y].qcoef;
+      qc.coef_d = bt.consts[blockIdx.y].qcoef_d;
+      qc.psi_g = bt.consts[blockIdx.y].fg;
+      qc.psi_q = bt.consts[blockIdx.y].fq;
+    }
+  }
+  constexpr int N = 1 << LOGN, MASK = N - 1, H = N / 2, LP = H + 1;
+  constexpr int TZ = QTiles<N>::TZ, NT = QTiles<N>::NT;
+  constexpr int NE = TZ * H, PER = (NE + NT - 1) / NT;          // own pairs of cells
+  constexpr int NS = (TZ + 2) * H, PS = (NS + NT - 1) / NT;     // with the rows around
+  constexpr int NB = TZ * LP > NS ? TZ * LP : NS;
+  __shared__ float2 buf[NB];
+  __shared__ float2 tws[N];
+  const int tid = threadIdx.x;
+  const int zb = (int)xcd_block(blockIdx.x, gridDim.x, TZ < 16 ? FDM_FFTZ_XG : 0);
+  const int x = zb / (N / TZ);
+  const int y0 = (zb % (N / TZ)) * TZ;
+  c2r_rows<LOGN, TZ, NT>(spec, tw, x, y0, buf, tws);
+  float2 ph[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int idx = tid + k * NT;
+    if (NE % NT == 0 || idx < NE) ph[k] = buf[idx / H * LP + idx % H];
+  }
+  auto at = [&](int px, int py, int z) {
+    return ((size_t)(px & MASK) * N + (py & MASK)) * N + z;
+  };
+  {
+    // s of rows y0 - 1 .. y0 + TZ, row r of them at buf[r * H]
+    float2 d[PS];
+#pragma unroll
+    for (int k = 0; k < PS; ++k) {
+      const int idx = tid + k * NT;
+      if (NS % NT == 0 || idx < NS)
+        d[k] = *reinterpret_cast<const float2*>(delta + at(x, y0 - 1 + idx / H, 2 * (idx % H)));
+    }
+    __syncthreads();   // every phi is in registers
+#pragma unroll
+    for (int k = 0; k < PS; ++k) {
+      const int idx = tid + k * NT;
+      if (NS % NT == 0 || idx < NS)
+        buf[idx] = make_float2(s_of<FIXED>(d[k].x, qc), s_of<FIXED>(d[k].y, qc));
+    }
+  }
+  __syncthreads();
+  const float near = sqrtf((float)qc.fp64_below) - 1.0f + 1e-6f;
+  const bool use64 = FIXED && qc.fp64_below > 0.0;
+  const float* s = reinterpret_cast<const float*>(buf);
+  double wsum = 0.0, usum = 0.0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int idx = tid + k * NT;
+    if (NE % NT == 0 || idx < NE) {
+      const int r = idx / H, z0 = 2 * (idx % H), y = y0 + r;
+      const float2 dp = *reinterpret_cast<const float2*>(delta + at(x + 1, y, z0));
+      const float2 dm = *reinterpret_cast<const float2*>(delta + at(x - 1, y, z0));
+      const float2 sc = buf[(r + 1) * H + idx % H], sm = buf[r * H + idx % H],
+                   sp = buf[(r + 2) * H + idx % H];
+      const float before = s[(r + 1) * N + ((z0 - 1) & MASK)];
+      const float after = s[(r + 1) * N + ((z0 + 2) & MASK)];
+      float qv[2], c2[2] = {sc.x, sc.y}, e2[2][3];
+      bool low[2] = {false, false};
+      float2 dc = make_float2(0.0f, 0.0f);
+      if constexpr (OUT == kOutEnergy || (FIXED && LOGN < 5))
+        dc = *reinterpret_cast<const float2*>(delta + at(x, y, z0));
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const float c = c2[j];
+        const float xp = s_of<FIXED>(j ? dp.y : dp.x, qc), xm = s_of<FIXED>(j ? dm.y : dm.x, qc);
+        const float yp = j ? sp.y : sp.x, ym = j ? sm.y : sm.x;
+        const float zp = j ? after : sc.y, zm = j ? sc.x : before;
+        const float nb = LOGN >= 5 ? (xm + xp) + ((ym + yp) + (zm + zp))
+                                   : (xp + xm) + (yp + ym) + (zp + zm);
+        const float lap = nb - 6.0f * c;
+        if constexpr (FIXED) {
+          qv[j] = qc.coef * lap * rcp_hw(1.0f + c);
+          low[j] = LOGN >= 5 ? use64 && c < near
+                             : (double)(1.0f + (j ? dc.y : dc.x)) < qc.fp64_below;
+        } else {
+          qv[j] = qc.coef * lap / c;
+        }
+        e2[j][0] = xp - c;
+        e2[j][1] = yp - c;
+        e2[j][2] = zp - c;
+      }
+      if constexpr (FIXED) {
+        if (low[0] || low[1]) {
+          // near-empty cells: sqrt(R) and Q in FP64 from the exact integer
+          // mass, for the pair together (it shares the values between)
+          auto pair = [&](int a, int b) {
+            return *reinterpret_cast<const longlong2*>(mass + at(a, b, z0));
+          };
+          const longlong2 mc = pair(x, y), mxp = pair(x + 1, y), mxm = pair(x - 1, y),
+                          myp = pair(x, y + 1), mym = pair(x, y - 1);
+          const long long mb = mass[at(x, y, (z0 - 1) & MASK)], ma = mass[at(x, y, (z0 + 2) & MASK)];
+          const double d0 = sqrt_r_of(mc.x, qc), d1 = sqrt_r_of(mc.y, qc);
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const double c0 = j ? d1 : d0;
+            if (low[j] && (LOGN < 5 || c0 * c0 < qc.fp64_below)) {
+              const double dxs = sqrt_r_of(j ? mxp.y : mxp.x, qc) + sqrt_r_of(j ? mxm.y : mxm.x, qc);
+              const double dys = sqrt_r_of(j ? myp.y : myp.x, qc) + sqrt_r_of(j ? mym.y : mym.x, qc);
+              const double dzs = j ? sqrt_r_of(ma, qc) + d0 : d1 + sqrt_r_of(mb, qc);
+              const double lapd = (dxs + dys + dzs) - 6.0 * c0;
+              qv[j] = (float)(qc.coef_d * lapd * rcp_d(c0));
+            }
+          }
+        }
+      }
+      float out[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const float p = j ? ph[k].y : ph[k].x;
+        out[j] = OUT == kOutPsi ? fmaf(qc.psi_q, qv[j], qc.psi_g * p) : qv[j];
+        if constexpr (OUT == kOutEnergy) {
+          wsum += (double)(j ? dc.y : dc.x) * (double)p;
+          const double e0 = (double)e2[j][0], e1 = (double)e2[j][1], e3 = (double)e2[j][2];
+          usum += e0 * e0 + e1 * e1 + e3 * e3;
+        }
+      }
+      if constexpr (OUT != kOutPsi) *reinterpret_cast<float2*>(phi + at(x, y, z0)) = ph[k];
+      *reinterpret_cast<float2*>(q + at(x, y, z0)) = make_float2(out[0], out[1]);
+    }
+  }
+  if constexpr (OUT == kOutEnergy) {
+    __shared__ double red[NT / 64];
+    const double ws = block_sum(wsum, red);
+    const double us = block_sum(usum, red);
+    if (threadIdx.x == 0) {
+      partials[2 * (size_t)blockIdx.x] = ws;
+      partials[2 * (size_t)blockIdx.x + 1] = us;
+    }
   }
 }
 
@@ -780,6 +963,47 @@ hipError_t launch_c2r_z(int logn, const float2* spec, const float2* tw, float* o
   }
   FDM_LOGN_SWITCH(logn, L_)
 #undef L_
+  return hipGetLastError();
+}
+
+int c2r_q_blocks(int logn) {
+  switch (logn) {
+#define B_(LN) \
+    case LN: return (1 << LN) * ((1 << LN) / QTiles<(1 << LN)>::TZ);
+    B_(4) B_(5) B_(6) B_(7) B_(8) B_(9)
+#undef B_
+    default: return 0;
+  }
+}
+
+hipError_t launch_c2r_q(int logn, bool fixed, int out, const float2* spec, const float2* tw,
+                        const float* delta, const void* mass, float* phi, float* q,
+                        const QConst& qc, double* partials, hipStream_t s, const Batch& bt) {
+  const dim3 g((unsigned)c2r_q_blocks(logn), bt.count);
+  const long long* m = static_cast<const long long*>(mass);
+#define K_(LN, FX, OUT)                                                                        \
+  hipLaunchKernelGGL((k_c2r_q<LN, FX, OUT>), g, dim3(QTiles<1 << LN>::NT), 0, s, spec, tw, delta, m, phi, q, \
+                     qc, partials, bt)
+#define O_(LN, FX)                    \
+  {                                   \
+    if (out == kOutPsi)               \
+      K_(LN, FX, kOutPsi);            \
+    else if (out == kOutEnergy)       \
+      K_(LN, FX, kOutEnergy);         \
+    else                              \
+      K_(LN, FX, kOutQ);              \
+  }
+#define L_(LN)          \
+  {                     \
+    if (fixed)          \
+      O_(LN, true)      \
+    else                \
+      O_(LN, false)     \
+  }
+  FDM_LOGN_SWITCH(logn, L_)
+#undef L_
+#undef O_
+#undef K_
   return hipGetLastError();
 }
 

@@ -165,8 +165,8 @@ struct QConst {
   double inv_mbar;        // 1 / mbar
   float psi_g, psi_q;     // kOutPsi: factors on phi and Q (a batch takes them per slot)
 };
-// What the Q stencil writes: Q; Q and the FP64 energy partials; or the
-// combined kick potential psi = psi_g * phi + psi_q * Q that the next gather
+// What the last pass of the solve writes: phi and Q; these and the FP64 energy
+// partials; or the combined kick potential psi = psi_g * phi + psi_q * Q that the next gather
 // differentiates (one mesh read per cell there instead of two).
 enum QOut : int { kOutQ = 0, kOutEnergy = 1, kOutPsi = 2 };
 
@@ -276,12 +276,17 @@ hipError_t launch_fft_x_green(int logn, float2* spec, const float2* tw, const fl
 hipError_t launch_c2r_z(int logn, const float2* spec, const float2* tw, float* out,
                         hipStream_t s, const Batch& bt = Batch());
 
+// Pass 5 and the Q stencil (out: a QOut; kOutPsi leaves phi alone);
+// c2r_q_blocks (delta phi, gradient) partials with kOutEnergy.
+int c2r_q_blocks(int logn);
+hipError_t launch_c2r_q(int logn, bool fixed, int out, const float2* spec, const float2* tw,
+                        const float* delta, const void* mass, float* phi, float* q,
+                        const QConst& qc, double* partials, hipStream_t s,
+                        const Batch& bt = Batch());
+
 // ---- stencil.hip
-hipError_t launch_qpot(int logn, bool fixed, int out, const float* delta,
-                       const long long* mass, const float* phi, float* q,
-                       const QConst& qc, double* partials, hipStream_t s,
-                       const Batch& bt = Batch());
-int qpot_blocks(int logn);
+hipError_t launch_qpot(int logn, bool fixed, const float* delta, const long long* mass, float* q,
+                       const QConst& qc, hipStream_t s);
 hipError_t launch_reduce(const double* partials, int nblocks, int ncomp, double* out,
                          hipStream_t s, const Batch& bt = Batch());
 // out[0..3] = K, W, U, K + W + U from the stencil's (delta phi, gradient)

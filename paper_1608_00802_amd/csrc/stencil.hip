@@ -9,72 +9,18 @@
 // exact integer mass (the 1/sqrt(rho) division is ill-conditioned there).
 // Plain FP32 form: sqrt(R) and the stencil directly in FP32.
 //
-// With kOutEnergy, each block also writes FP64 partial sums of delta*phi (for
-// the potential energy) and of sum_d (sqrt R_{j+e_d} - sqrt R_j)^2 (gradient
-// energy K_rho of Eq. (6), forward differences); a single-block kernel reduces
-// the partials in a fixed order, so the totals are deterministic.  With
-// kOutPsi the output is psi_g * phi + psi_q * Q instead of Q.
+// This is the stencil alone (pm_qpot).  Inside a solve it runs in the last
+// pass of the Poisson solve, which also forms the kick potential and the
+// energy sums; the small kernels that reduce those sums are here.
 #include "internal.h"
+#include "qpot.h"
 
 namespace fdm {
 
-// Fixed-point form: the hardware square root and reciprocal (about 1 ulp
-// each; arguments stay in the normal range, r >= the density floor), which
-// keep s to a few ulp relative at every delta.  Q in FP32 is ~7 us faster
-// at 256^3 than with correctly rounded sqrtf and division.
-__device__ __forceinline__ float sqrt_hw(float x) { return __builtin_amdgcn_sqrtf(x); }
-__device__ __forceinline__ float rcp_hw(float x) { return __builtin_amdgcn_rcpf(x); }
-
-// FP64 square root and reciprocal for the near-empty path: the hardware
-// single-precision estimate refined by two Newton steps in FP64 (relative
-// error a few 1e-16 for the positive normal arguments used here), several
-// times cheaper than the correctly rounded library forms.
-__device__ __forceinline__ double sqrt_d(double r) {
-  double y = (double)__builtin_amdgcn_rsqf((float)r);   // ~1/sqrt(r), single precision
-  y = y * (1.5 - 0.5 * r * y * y);
-  y = y * (1.5 - 0.5 * r * y * y);
-  return r * y;
-}
-__device__ __forceinline__ double rcp_d(double x) {
-  double y = (double)__builtin_amdgcn_rcpf((float)x);   // ~1/x, single precision
-  y = y * (2.0 - x * y);
-  y = y * (2.0 - x * y);
-  return y;
-}
-
-__device__ __forceinline__ double block_sum(double v, double* red) {
-  // wave64 shuffle reduction, then across the block's waves through LDS
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) red[wave] = v;
-  __syncthreads();
-  double t = 0.0;
-  if (threadIdx.x == 0)
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += red[w];
-  __syncthreads();
-  return t;
-}
-
-template <int LOGN, bool FIXED, int OUT>
+template <int LOGN, bool FIXED>
 __global__ void __launch_bounds__(kBlock) k_qpot(const float* __restrict__ delta,
                                                  const long long* __restrict__ mass,
-                                                 const float* __restrict__ phi,
-                                                 float* __restrict__ q, QConst qc,
-                                                 double* __restrict__ partials, Batch bt) {
-  {
-    const int sl = bslot(bt);
-    delta = woff(delta, bt, sl);
-    mass = woff(mass, bt, sl);
-    phi = woff(phi, bt, sl);
-    q = woff(q, bt, sl);
-    partials = woff(partials, bt, sl);
-    if (bt.consts) {
-      qc.coef = bt.consts[blockIdx.y].qcoef;
-      qc.coef_d = bt.consts[blockIdx.y].qcoef_d;
-      qc.psi_g = bt.consts[blockIdx.y].fg;
-      qc.psi_q = bt.consts[blockIdx.y].fq;
-    }
-  }
+                                                 float* __restrict__ q, QConst qc) {
   constexpr int N = 1 << LOGN;
   constexpr int MASK = N - 1;
   const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
@@ -122,22 +68,7 @@ __global__ void __launch_bounds__(kBlock) k_qpot(const float* __restrict__ delta
     const float lap = ((sn[0] + sn[1]) + (sn[2] + sn[3]) + (sn[4] + sn[5])) - 6.0f * sc;
     qv = qc.coef * lap / sc;
   }
-  if constexpr (OUT == kOutPsi)
-    q[i] = fmaf(qc.psi_q, qv, qc.psi_g * phi[i]);
-  else
-    q[i] = qv;
-  if constexpr (OUT == kOutEnergy) {
-    __shared__ double red[kBlock / 64];
-    const double w = (double)dc * (double)phi[i];
-    const double e0 = (double)(sn[0] - sc), e1 = (double)(sn[2] - sc), e2 = (double)(sn[4] - sc);
-    const double u = e0 * e0 + e1 * e1 + e2 * e2;
-    const double ws = block_sum(w, red);
-    const double us = block_sum(u, red);
-    if (threadIdx.x == 0) {
-      partials[2 * (size_t)blockIdx.x] = ws;
-      partials[2 * (size_t)blockIdx.x + 1] = us;
-    }
-  }
+  q[i] = qv;
 }
 
 // Tiled version (N >= 32): a block owns a QY x QZ column of (y, z) and sweeps
@@ -168,33 +99,10 @@ constexpr int kQBlock = QY * QZ;   // threads per block of the tiled stencil
 #endif
 static_assert(kQBlock % 64 == 0 && kQBlock / 64 <= 64, "whole waves, one flag per lane");
 
-template <bool FIXED>
-__device__ __forceinline__ float s_of(float d, const QConst& qc) {
-  const float r = 1.0f + d;
-  if constexpr (FIXED) return (r >= qc.floor_f) ? d * rcp_hw(1.0f + sqrt_hw(r)) : qc.s_floor;
-  return sqrtf(r >= qc.floor_f ? r : qc.floor_f);
-}
-
-template <int LOGN, bool FIXED, int OUT>
-__global__ void __launch_bounds__(kQBlock, OUT == kOutEnergy ? 1 : 8) k_qpot_tiled(const float* __restrict__ delta,
-                                                       const long long* __restrict__ mass,
-                                                       const float* __restrict__ phi,
-                                                       float* __restrict__ q, QConst qc,
-                                                       double* __restrict__ partials, Batch bt) {
-  {
-    const int sl = bslot(bt);
-    delta = woff(delta, bt, sl);
-    mass = woff(mass, bt, sl);
-    phi = woff(phi, bt, sl);
-    q = woff(q, bt, sl);
-    partials = woff(partials, bt, sl);
-    if (bt.consts) {
-      qc.coef = bt.consts[blockIdx.y].qcoef;
-      qc.coef_d = bt.consts[blockIdx.y].qcoef_d;
-      qc.psi_g = bt.consts[blockIdx.y].fg;
-      qc.psi_q = bt.consts[blockIdx.y].fq;
-    }
-  }
+template <int LOGN, bool FIXED>
+__global__ void __launch_bounds__(kQBlock, 8) k_qpot_tiled(const float* __restrict__ delta,
+                                                           const long long* __restrict__ mass,
+                                                           float* __restrict__ q, QConst qc) {
   constexpr int N = 1 << LOGN;
   constexpr int MASK = N - 1;
   constexpr int PY = QY + 2, PZ = QZ + 2;
@@ -261,11 +169,7 @@ __global__ void __launch_bounds__(kQBlock, OUT == kOutEnergy ? 1 : 8) k_qpot_til
     const uint32_t f = lane < kQBlock / 64 ? nflag[slot][lane] : 0u;
     return (bool)__any(f != 0u);
   };
-  auto sdv = [&](long long m) {
-    double r = (double)m * qc.inv_mbar;
-    r = r > qc.floor_d ? r : qc.floor_d;
-    return sqrt_d(r);
-  };
+  auto sdv = [&](long long m) { return sqrt_r_of(m, qc); };
   auto sd = [&](size_t j) { return sdv(mass[j]); };
   // The integer mass of the next plane, loaded while this one is computed
   // once the next plane is known to hold a near-empty cell (block-uniform),
@@ -279,16 +183,7 @@ __global__ void __launch_bounds__(kQBlock, OUT == kOutEnergy ? 1 : 8) k_qpot_til
   auto inplane = [&](const float* buf) {
     return (buf[cc - PZ] + buf[cc + PZ]) + (buf[cc - 1] + buf[cc + 1]);
   };
-  auto phi_at = [&](int x) { return phi[((size_t)x * N + y) * N + z]; };
-  double wsum = 0.0, usum = 0.0;
   float s_prev = s_of<FIXED>(delta[((size_t)((x0 - 1) & MASK) * N + y) * N + z], qc);
-  // phi of the own column, two planes ahead (psi and energy outputs), in the
-  // slot of the plane's parity
-  float phA = 0.0f, phB = 0.0f;
-  if constexpr (OUT != kOutQ) {
-    phA = phi_at(x0);
-    phB = phi_at(x0 + 1);
-  }
   fetch(x0, preA);
   commit(pl[0], 0, preA);
   fetch(x0 + 1, preB);
@@ -297,11 +192,10 @@ __global__ void __launch_bounds__(kQBlock, OUT == kOutEnergy ? 1 : 8) k_qpot_til
   bool near_cur = plane_near(0);                  // plane x holds a near-empty cell
   float s_cur = pl[0][cc];
   float in_cur = inplane(pl[0]);
-  float sy_cur = pl[0][cc + PZ], sz_cur = pl[0][cc + 1];
   double d_prev = 0.0;                            // FP64 sqrt(R) of plane x - 1, own column
   // plane x: its successor x + 1 sits in `nxt` (loads issued two planes ago),
-  // which then takes plane x + 3; `ph` holds phi of plane x and then x + 2
-  auto plane = [&](int x, float (&nxt)[PER], float& ph) {
+  // which then takes plane x + 3
+  auto plane = [&](int x, float (&nxt)[PER]) {
     const int nbi = (x - x0 + 1) & 1;
     float* nb = pl[nbi];
     commit(nb, nbi, nxt);                     // plane x + 1
@@ -310,7 +204,6 @@ __global__ void __launch_bounds__(kQBlock, OUT == kOutEnergy ? 1 : 8) k_qpot_til
     const bool near_next = plane_near(nbi);
     const float s_next = nb[cc];
     const float in_next = inplane(nb);
-    const float sy_next = nb[cc + PZ], sz_next = nb[cc + 1];
     // FP64 values of plane x: needed by its own near-empty cells and, as the
     // x - 1 neighbour, by those of plane x + 1 (block-uniform condition)
     double d_c = 0.0, d_ym = 0.0, d_yp = 0.0, d_zm = 0.0, d_zp = 0.0;
@@ -363,96 +256,44 @@ __global__ void __launch_bounds__(kQBlock, OUT == kOutEnergy ? 1 : 8) k_qpot_til
     } else {
       qv = qc.coef * lap / s_cur;
     }
-    if constexpr (OUT == kOutPsi)
-      q[i] = fmaf(qc.psi_q, qv, qc.psi_g * ph);
-    else
-      q[i] = qv;
-    if constexpr (OUT == kOutEnergy) {
-      wsum += (double)delta[i] * (double)ph;
-      const double e0 = (double)(s_next - s_cur), e1 = (double)(sy_cur - s_cur),
-                   e2 = (double)(sz_cur - s_cur);
-      usum += e0 * e0 + e1 * e1 + e2 * e2;
-    }
-    if constexpr (OUT != kOutQ)
-      if (x + 2 < x0 + QX) ph = phi_at(x + 2);
+    q[i] = qv;
     s_prev = s_cur;
     s_cur = s_next;
     in_cur = in_next;
-    sy_cur = sy_next;
-    sz_cur = sz_next;
     d_prev = d_c;
     near_cur = near_next;
   };
   static_assert(QX % 2 == 0, "planes go in pairs");
   for (int x = x0; x < x0 + QX; x += 2) {
-    plane(x, preB, phA);
-    plane(x + 1, preA, phB);
-  }
-  if constexpr (OUT == kOutEnergy) {
-    __shared__ double red[kQBlock / 64];
-    const double ws = block_sum(wsum, red);
-    const double us = block_sum(usum, red);
-    if (threadIdx.x == 0) {
-      partials[2 * (size_t)blockIdx.x] = ws;
-      partials[2 * (size_t)blockIdx.x + 1] = us;
-    }
+    plane(x, preB);
+    plane(x + 1, preA);
   }
 }
 
-int qpot_blocks(int logn) {
-#ifndef FDM_QPOT_SIMPLE
+static int qpot_blocks(int logn) {
   if (logn >= 5) return (int)(((size_t)1 << (3 * logn)) / ((size_t)QY * QZ * qpot_qx(logn)));
-#endif
   return (int)(((size_t)1 << (3 * logn)) / kBlock);
 }
 
-hipError_t launch_qpot(int logn, bool fixed, int out, const float* delta,
-                       const long long* mass, const float* phi, float* q, const QConst& qc,
-                       double* partials, hipStream_t s, const Batch& bt) {
-  const dim3 g((unsigned)qpot_blocks(logn), bt.count);
-  if (out != kOutQ && out != kOutEnergy && out != kOutPsi) return hipErrorInvalidValue;
-#define K_(KERNEL, LN, FX, TB)                                                               \
-  {                                                                                          \
-    if (out == kOutEnergy)                                                                   \
-      hipLaunchKernelGGL((KERNEL<LN, FX, kOutEnergy>), g, dim3(TB), 0, s, delta, mass,        \
-                         phi, q, qc, partials, bt);                                          \
-    else if (out == kOutPsi)                                                                 \
-      hipLaunchKernelGGL((KERNEL<LN, FX, kOutPsi>), g, dim3(TB), 0, s, delta, mass, phi,      \
-                         q, qc, partials, bt);                                               \
-    else                                                                                     \
-      hipLaunchKernelGGL((KERNEL<LN, FX, kOutQ>), g, dim3(TB), 0, s, delta, mass, phi, q,     \
-                         qc, partials, bt);                                                  \
+hipError_t launch_qpot(int logn, bool fixed, const float* delta, const long long* mass, float* q,
+                       const QConst& qc, hipStream_t s) {
+  const dim3 g((unsigned)qpot_blocks(logn));
+#define K_(KERNEL, LN, TB)                                                               \
+  {                                                                                      \
+    if (fixed)                                                                           \
+      hipLaunchKernelGGL((KERNEL<LN, true>), g, dim3(TB), 0, s, delta, mass, q, qc);     \
+    else                                                                                 \
+      hipLaunchKernelGGL((KERNEL<LN, false>), g, dim3(TB), 0, s, delta, mass, q, qc);    \
   }
-#ifndef FDM_QPOT_SIMPLE
-  if (logn >= 5) {
-#define T_(LN)                          \
-  {                                     \
-    if (fixed)                          \
-      K_(k_qpot_tiled, LN, true, kQBlock)  \
-    else                                \
-      K_(k_qpot_tiled, LN, false, kQBlock) \
+  switch (logn) {
+    case 4: K_(k_qpot, 4, kBlock); break;
+    case 5: K_(k_qpot_tiled, 5, kQBlock); break;
+    case 6: K_(k_qpot_tiled, 6, kQBlock); break;
+    case 7: K_(k_qpot_tiled, 7, kQBlock); break;
+    case 8: K_(k_qpot_tiled, 8, kQBlock); break;
+    case 9: K_(k_qpot_tiled, 9, kQBlock); break;
+    default: return hipErrorInvalidValue;
   }
-    switch (logn) {
-      case 5: T_(5); break;
-      case 6: T_(6); break;
-      case 7: T_(7); break;
-      case 8: T_(8); break;
-      case 9: T_(9); break;
-      default: return hipErrorInvalidValue;
-    }
-#undef T_
-    return hipGetLastError();
-  }
-#endif
-#define L_(LN)                   \
-  {                              \
-    if (fixed)                   \
-      K_(k_qpot, LN, true, kBlock)  \
-    else                         \
-      K_(k_qpot, LN, false, kBlock) \
-  }
-  FDM_LOGN_SWITCH(logn, L_)
-#undef L_
 #undef K_
   return hipGetLastError();
 }

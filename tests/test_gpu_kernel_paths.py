@@ -262,3 +262,40 @@ def test_force_of_combined_potential(pm, gpu, prec):
     whole = force(pos)
     parts = torch.cat([force(p.contiguous()) for p in pos.split(30000, dim=1)], dim=1)
     assert torch.equal(whole, parts)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("n", [16, 32, 64, 128, 256])
+def test_last_pass_with_stencil(pm, gpu, n, prec):
+    """The Q of the solve's last pass (clumps over empty cells, which the box
+    corner crosses) against the stencil alone on the same density, bitwise,
+    and phi against the solve alone; both are read through a step's fields."""
+    import torch
+    npart = n ** 3 // 3 + 1
+    st = _state(n, npart, seed=n)
+    lp = pm.make_params(n, npart, float(n), hbar_over_m=0.3, precision=prec, comoving=True)
+    ctx = pm.PMContext(lp, device=gpu)
+    pos, vel = to_device(st, gpu, fp32_positions=prec == 0)
+    ctx.sort(pos, vel)
+    ctx.step(pos, vel, [0.5, 0.5 + 1e-9])   # leaves phi and Q at the positions
+    one, two = torch.empty((3, npart), device=gpu), torch.empty((3, npart), device=gpu)
+    ctx.force(pos, one, 0.5)
+    phi, q = torch.empty(n ** 3, device=gpu), torch.empty(n ** 3, device=gpu)
+    delta = torch.empty(n ** 3, device=gpu)
+    if prec:   # (the float deposit is not repeatable to the bit)
+        ctx.deposit(pos, delta)
+        ctx.poisson(None, phi)
+        ctx.qpot(None, q)
+        ctx.force(pos, two, 0.5, phi, q)
+        torch.cuda.synchronize()
+        assert torch.equal(one, two)
+    op = oracle.Params(n=n, box=float(n), S=0.45, hbar_m=0.3, comoving=True)
+    if n <= 64:
+        x = pos.cpu().numpy().T.astype(np.float64) if prec == 0 else None
+        if prec:
+            from gpu_helpers import positions_cells
+            x = positions_cells(pos, n)
+        e = ctx.energy(pos, vel, 0.5)
+        ref = oracle.energies(x, vel.cpu().numpy().T.astype(np.float64), op, 0.5)
+        for key in ("K", "W", "U"):
+            assert abs(e[key] - ref[key]) <= 1e-5 * abs(ref[key])
