@@ -279,43 +279,46 @@ const Gauss& gauss() {
   return g;
 }
 
-double hubble(const pm_params& p, double a) {
-  return p.h0 * sqrt(p.omega_m / (a * a * a) + p.omega_l);
-}
-
-// int_{a0}^{a1} da / (a^pw H(a)), composite Gauss-Legendre in s = ln a
-double a_integral(const pm_params& p, double a0, double a1, int pw) {
-  const Gauss& g = gauss();
-  const double s0 = log(a0), s1 = log(a1);
-  int m = (int)ceil(fabs(s1 - s0) / 0.02);
-  if (m < 1) m = 1;
-  const double hseg = (s1 - s0) / m;
-  double total = 0.0;
-  for (int k = 0; k < m; ++k) {
-    const double c = s0 + (k + 0.5) * hseg;
-    double part = 0.0;
-    for (int i = 0; i < Gauss::n; ++i) {
-      const double s = c + 0.5 * hseg * g.x[i];
-      const double a = exp(s);
-      part += g.w[i] * a / (pow(a, pw) * hubble(p, a));  // da = a ds
-    }
-    total += 0.5 * hseg * part;
-  }
-  return total;
-}
+double hubble(const pm_params& p, double a3) { return p.h0 * sqrt(p.omega_m / a3 + p.omega_l); }
 
 struct Kick {
   double g, q;
 };
 
+// int_{a0}^{a1} da / (a^2 H(a)) (g) and da / (a^3 H(a)) (q), composite
+// Gauss-Legendre in s = ln a: one evaluation of the nodes for both, the powers
+// multiplied out (a call of 64 runs and ten steps needs 1920 of these on the
+// host: 891 -> 309 us for the call, against 1.0 ms of GPU time).
+Kick a_integrals(const pm_params& p, double a0, double a1) {
+  const Gauss& g = gauss();
+  const double s0 = log(a0), s1 = log(a1);
+  int m = (int)ceil(fabs(s1 - s0) / 0.02);
+  if (m < 1) m = 1;
+  const double hseg = (s1 - s0) / m;
+  Kick total = {0.0, 0.0};
+  for (int k = 0; k < m; ++k) {
+    const double c = s0 + (k + 0.5) * hseg;
+    Kick part = {0.0, 0.0};
+    for (int i = 0; i < Gauss::n; ++i) {
+      const double a = exp(c + 0.5 * hseg * g.x[i]);
+      const double a2 = a * a, a3 = a2 * a, h = hubble(p, a3);
+      part.g += g.w[i] * a / (a2 * h);  // da = a ds
+      part.q += g.w[i] * a / (a3 * h);
+    }
+    total.g += 0.5 * hseg * part.g;
+    total.q += 0.5 * hseg * part.q;
+  }
+  return total;
+}
+
 Kick kick(const pm_params& p, double t0, double t1) {
   if (!p.comoving) return {t1 - t0, t1 - t0};
-  return {a_integral(p, t0, t1, 2), a_integral(p, t0, t1, 3)};
+  return a_integrals(p, t0, t1);
 }
 
 double drift(const pm_params& p, double t0, double t1) {
   if (!p.comoving) return t1 - t0;
-  return a_integral(p, t0, t1, 3);
+  return a_integrals(p, t0, t1).q;
 }
 
 double midpoint(const pm_params& p, double t0, double t1) {
