@@ -246,6 +246,7 @@ __device__ __forceinline__ void fft_first(float2 (&v)[F1], int n2, const float2*
 template <int LOGN, int SRC>
 __global__ void __launch_bounds__(kZBlock) k_r2c_z(const void* __restrict__ in,
                                                   float* __restrict__ delta_out,
+                                                  float* __restrict__ delta_too,
                                                   float2* __restrict__ spec,
                                                   const float2* __restrict__ tw, DeltaConv conv,
                                                   Batch bt) {
@@ -293,13 +294,15 @@ __global__ void __launch_bounds__(kZBlock) k_r2c_z(const void* __restrict__ in,
         if constexpr (SRC == kSrcMass64) {
           d.x = (float)((double)(m[k].x - conv.mbar) / conv.dmbar);
           d.y = (float)((double)(m[k].y - conv.mbar) / conv.dmbar);
-          *reinterpret_cast<float2*>(delta_out + cell) = d;
         } else if constexpr (SRC == kSrcAcc32) {
           d.x = a[k].x * conv.acc_norm - 1.0f;
           d.y = a[k].y * conv.acc_norm - 1.0f;
-          *reinterpret_cast<float2*>(delta_out + cell) = d;
         } else {
           d = a[k];
+        }
+        if constexpr (SRC != kSrcDelta) {
+          *reinterpret_cast<float2*>(delta_out + cell) = d;
+          if (delta_too) *reinterpret_cast<float2*>(delta_too + cell) = d;
         }
         buf[r * LP + n] = d;
       }
@@ -575,12 +578,8 @@ __device__ __forceinline__ void c2r_rows(const float2* __restrict__ spec,
 template <int LOGN>
 __global__ void __launch_bounds__(kZBlock) k_c2r_z(const float2* __restrict__ spec,
                                                   const float2* __restrict__ tw,
-                                                  float* __restrict__ out, Batch bt) {
-  {
-    const int sl = bslot(bt);
-    spec = woff(spec, bt, sl);
-    out = woff(out, bt, sl);
-  }
+                                                  float* __restrict__ out,
+                                                  float* __restrict__ out_too) {
   constexpr int N = 1 << LOGN, H = N / 2, LP = H + 1, TZ = Tiles<N>::TZ;
   __shared__ float2 buf[TZ * LP];
   __shared__ float2 tws[N];
@@ -591,7 +590,10 @@ __global__ void __launch_bounds__(kZBlock) k_c2r_z(const float2* __restrict__ sp
   c2r_rows<LOGN, TZ, kZBlock>(spec, tw, x, y0, buf, tws);
   for (int idx = tid; idx < TZ * H; idx += kZBlock) {
     const int r = idx / H, n = idx % H;
-    *reinterpret_cast<float2*>(out + ((size_t)x * N + y0 + r) * N + 2 * n) = buf[r * LP + n];
+    const size_t cell = ((size_t)x * N + y0 + r) * N + 2 * n;
+    const float2 v = buf[r * LP + n];
+    *reinterpret_cast<float2*>(out + cell) = v;
+    if (out_too) *reinterpret_cast<float2*>(out_too + cell) = v;
   }
 }
 
@@ -769,20 +771,21 @@ __global__ void __launch_bounds__(QTiles<1 << LOGN>::NT) k_c2r_q(const float2* _
 
 // ---------------------------------------------------------------- launchers
 hipError_t launch_r2c_z(int logn, int src, const void* in, float* delta_out, float2* spec,
-                        const float2* tw, DeltaConv conv, hipStream_t s, const Batch& bt) {
+                        const float2* tw, DeltaConv conv, hipStream_t s, const Batch& bt,
+                        float* delta_too) {
 #define L_(LN)                                                                          \
   {                                                                                     \
     constexpr int N_ = 1 << LN;                                                         \
     dim3 g(N_ * (N_ / Tiles<N_>::TZ), bt.count);                                        \
     if (src == kSrcMass64)                                                              \
       hipLaunchKernelGGL((k_r2c_z<LN, kSrcMass64>), g, dim3(kZBlock), 0, s, in, delta_out, \
-                         spec, tw, conv, bt);                                           \
+                         delta_too, spec, tw, conv, bt);                                           \
     else if (src == kSrcAcc32)                                                          \
       hipLaunchKernelGGL((k_r2c_z<LN, kSrcAcc32>), g, dim3(kZBlock), 0, s, in, delta_out, \
-                         spec, tw, conv, bt);                                           \
+                         delta_too, spec, tw, conv, bt);                                           \
     else                                                                                \
       hipLaunchKernelGGL((k_r2c_z<LN, kSrcDelta>), g, dim3(kZBlock), 0, s, in, delta_out, \
-                         spec, tw, conv, bt);                                           \
+                         delta_too, spec, tw, conv, bt);                                           \
   }
   FDM_LOGN_SWITCH(logn, L_)
 #undef L_
@@ -954,12 +957,12 @@ hipError_t launch_fft_x_power(int logn, const float2* spec, const float2* tw, in
 }
 
 hipError_t launch_c2r_z(int logn, const float2* spec, const float2* tw, float* out,
-                        hipStream_t s, const Batch& bt) {
+                        hipStream_t s, float* out_too) {
 #define L_(LN)                                                                  \
   {                                                                             \
     constexpr int N_ = 1 << LN;                                                 \
-    dim3 g(N_ * (N_ / Tiles<N_>::TZ), bt.count);                                \
-    hipLaunchKernelGGL((k_c2r_z<LN>), g, dim3(kZBlock), 0, s, spec, tw, out, bt); \
+    dim3 g(N_ * (N_ / Tiles<N_>::TZ));                                          \
+    hipLaunchKernelGGL((k_c2r_z<LN>), g, dim3(kZBlock), 0, s, spec, tw, out, out_too); \
   }
   FDM_LOGN_SWITCH(logn, L_)
 #undef L_

@@ -265,16 +265,18 @@ hipError_t launch_sort_copy(uint32_t* pos, float* vel, const uint32_t* pos_tmp,
 
 // ---- fft.hip
 // Forward transform of the density contrast and Poisson solve, written as
-// five passes over the half-spectrum spec[kz][kx][ky] (kz = 0..N/2).
+// five passes over the half-spectrum spec[kz][kx][ky] (kz = 0..N/2).  The
+// *_too outputs (8-byte aligned, or null) receive the same values again: a
+// caller's copy without a pass of its own.
 hipError_t launch_r2c_z(int logn, int src, const void* in, float* delta_out,
                         float2* spec, const float2* tw, DeltaConv conv, hipStream_t s,
-                        const Batch& bt = Batch());
+                        const Batch& bt = Batch(), float* delta_too = nullptr);
 hipError_t launch_fft_y(int logn, float2* spec, const float2* tw, bool inverse,
                         hipStream_t s, const Batch& bt = Batch());
 hipError_t launch_fft_x_green(int logn, float2* spec, const float2* tw, const float* s2,
                               float green_scale, hipStream_t s, const Batch& bt = Batch());
 hipError_t launch_c2r_z(int logn, const float2* spec, const float2* tw, float* out,
-                        hipStream_t s, const Batch& bt = Batch());
+                        hipStream_t s, float* out_too = nullptr);
 
 // Pass 5 and the Q stencil (out: a QOut; kOutPsi leaves phi alone);
 // c2r_q_blocks (delta phi, gradient) partials with kOutEnergy.
@@ -285,8 +287,9 @@ hipError_t launch_c2r_q(int logn, bool fixed, int out, const float2* spec, const
                         const Batch& bt = Batch());
 
 // ---- stencil.hip
+// (q_too as above, any float alignment)
 hipError_t launch_qpot(int logn, bool fixed, const float* delta, const long long* mass, float* q,
-                       const QConst& qc, hipStream_t s);
+                       float* q_too, const QConst& qc, hipStream_t s);
 hipError_t launch_reduce(const double* partials, int nblocks, int ncomp, double* out,
                          hipStream_t s, const Batch& bt = Batch());
 // out[0..3] = K, W, U, K + W + U from the stencil's (delta phi, gradient)

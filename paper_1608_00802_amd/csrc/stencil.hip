@@ -20,7 +20,8 @@ namespace fdm {
 template <int LOGN, bool FIXED>
 __global__ void __launch_bounds__(kBlock) k_qpot(const float* __restrict__ delta,
                                                  const long long* __restrict__ mass,
-                                                 float* __restrict__ q, QConst qc) {
+                                                 float* __restrict__ q,
+                                                           float* __restrict__ q_too, QConst qc) {
   constexpr int N = 1 << LOGN;
   constexpr int MASK = N - 1;
   const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
@@ -69,6 +70,7 @@ __global__ void __launch_bounds__(kBlock) k_qpot(const float* __restrict__ delta
     qv = qc.coef * lap / sc;
   }
   q[i] = qv;
+  if (q_too) q_too[i] = qv;
 }
 
 // Tiled version (N >= 32): a block owns a QY x QZ column of (y, z) and sweeps
@@ -102,7 +104,8 @@ static_assert(kQBlock % 64 == 0 && kQBlock / 64 <= 64, "whole waves, one flag pe
 template <int LOGN, bool FIXED>
 __global__ void __launch_bounds__(kQBlock, 8) k_qpot_tiled(const float* __restrict__ delta,
                                                            const long long* __restrict__ mass,
-                                                           float* __restrict__ q, QConst qc) {
+                                                           float* __restrict__ q,
+                                                           float* __restrict__ q_too, QConst qc) {
   constexpr int N = 1 << LOGN;
   constexpr int MASK = N - 1;
   constexpr int PY = QY + 2, PZ = QZ + 2;
@@ -257,6 +260,7 @@ __global__ void __launch_bounds__(kQBlock, 8) k_qpot_tiled(const float* __restri
       qv = qc.coef * lap / s_cur;
     }
     q[i] = qv;
+    if (q_too) q_too[i] = qv;
     s_prev = s_cur;
     s_cur = s_next;
     in_cur = in_next;
@@ -276,14 +280,14 @@ static int qpot_blocks(int logn) {
 }
 
 hipError_t launch_qpot(int logn, bool fixed, const float* delta, const long long* mass, float* q,
-                       const QConst& qc, hipStream_t s) {
+                       float* q_too, const QConst& qc, hipStream_t s) {
   const dim3 g((unsigned)qpot_blocks(logn));
 #define K_(KERNEL, LN, TB)                                                               \
   {                                                                                      \
     if (fixed)                                                                           \
-      hipLaunchKernelGGL((KERNEL<LN, true>), g, dim3(TB), 0, s, delta, mass, q, qc);     \
+      hipLaunchKernelGGL((KERNEL<LN, true>), g, dim3(TB), 0, s, delta, mass, q, q_too, qc); \
     else                                                                                 \
-      hipLaunchKernelGGL((KERNEL<LN, false>), g, dim3(TB), 0, s, delta, mass, q, qc);    \
+      hipLaunchKernelGGL((KERNEL<LN, false>), g, dim3(TB), 0, s, delta, mass, q, q_too, qc); \
   }
   switch (logn) {
     case 4: K_(k_qpot, 4, kBlock); break;

@@ -299,3 +299,36 @@ def test_last_pass_with_stencil(pm, gpu, n, prec):
         ref = oracle.energies(x, vel.cpu().numpy().T.astype(np.float64), op, 0.5)
         for key in ("K", "W", "U"):
             assert abs(e[key] - ref[key]) <= 1e-5 * abs(ref[key])
+
+
+@pytest.mark.parametrize("n", [16, 32, 64])
+def test_mesh_outputs_of_the_composable_calls(pm, gpu, n):
+    """The meshes a caller gets: written by the kernels (aligned), copied
+    (one float off an 8-byte boundary), over the input, and from the spectrum
+    that the deposit leaves or from a fresh transform -- the same each time."""
+    import torch
+    npart = n ** 3 // 2
+    ctx = pm.PMContext(pm.make_params(n, npart, float(n), hbar_over_m=0.3), device=gpu)
+    pos, _ = to_device(_state(n, npart, seed=2 * n), gpu)
+    odd = [torch.empty(n ** 3 + 1, device=gpu)[1:] for _ in range(3)]
+    even = [torch.empty(n ** 3, device=gpu) for _ in range(3)]
+    for delta, phi, q in (even, odd):
+        ctx.deposit(pos, delta)
+        ctx.poisson(None, phi)
+        ctx.qpot(None, q)
+    again = torch.empty(n ** 3, device=gpu)
+    ctx.poisson(None, again)            # the spectrum is gone: a fresh transform
+    given = torch.empty(n ** 3, device=gpu)
+    ctx.poisson(even[0], given)
+    over = even[0].clone()
+    apart = torch.empty(n ** 3, device=gpu)
+    ctx.qpot(over, over)
+    ctx.qpot(even[0], apart)
+    both = even[0].clone()
+    ctx.poisson(both, both)
+    torch.cuda.synchronize()
+    for a, b in zip(even, odd):
+        assert torch.equal(a, b)
+    for a in (again, given, both):
+        assert torch.equal(a, even[1])
+    assert torch.equal(over, apart)
