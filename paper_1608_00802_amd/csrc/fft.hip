@@ -44,6 +44,26 @@ __device__ __forceinline__ float2 cscale(float2 a, float s) { return make_float2
 
 constexpr int ilog2c(int v) { return v <= 1 ? 0 : 1 + ilog2c(v >> 1); }
 
+// Loads that need not stay in the caches: the mass mesh, which only near-empty
+// cells read again, and the spectrum in its last pass.  At 256^3, where the
+// meshes of a solve about fill the 256 MB cache, the spectrum that the z pass
+// writes then stays there for the y pass: z 56 -> 49 us, y 30 -> 24 us; 512^3
+// solve 1.59 -> 1.57 ms.  (The same on the gather's particles, read and
+// written once a step, made it slower: 272 -> 275-294 us.)
+__device__ __forceinline__ longlong2 load_once(const long long* p) {
+  typedef long long v2 __attribute__((ext_vector_type(2)));
+  const v2 v = __builtin_nontemporal_load(reinterpret_cast<const v2*>(p));
+  longlong2 r;
+  r.x = v.x;
+  r.y = v.y;
+  return r;
+}
+__device__ __forceinline__ float2 load_once(const float2* p) {
+  typedef float v2 __attribute__((ext_vector_type(2)));
+  const v2 v = __builtin_nontemporal_load(reinterpret_cast<const v2*>(p));
+  return make_float2(v.x, v.y);
+}
+
 // ROWS independent length-L complex FFTs on LDS rows buf[r*(L+1) + n].
 // tw[k*TWS] = exp(-2 pi i k / L).  Forward: exp(-i); INV: exp(+i), no scaling.
 template <int L, int ROWS, int NT, int TWS, bool INV>
@@ -279,7 +299,7 @@ __global__ void __launch_bounds__(kZBlock) k_r2c_z(const void* __restrict__ in,
       if (NE % kZBlock == 0 || idx < NE) {
         const size_t cell = ((size_t)x * N + y0 + idx / H) * N + 2 * (idx % H);
         if constexpr (SRC == kSrcMass64)
-          m[k] = *reinterpret_cast<const longlong2*>((const long long*)in + cell);
+          m[k] = load_once((const long long*)in + cell);
         else
           a[k] = *reinterpret_cast<const float2*>((const float*)in + cell);
       }
@@ -551,7 +571,7 @@ __device__ __forceinline__ void c2r_rows(const float2* __restrict__ spec,
     for (int k = 0; k < PER; ++k) {
       const int idx = tid + k * NT;
       if (NE % NT == 0 || idx < NE)
-        v[k] = spec[((size_t)(idx / TZ) * N + x) * N + y0 + idx % TZ];
+        v[k] = load_once(&spec[((size_t)(idx / TZ) * N + x) * N + y0 + idx % TZ]);
     }
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
