@@ -42,9 +42,10 @@ def alg_bytes(n: int, npart: int, steps: int = 20) -> dict:
     cells: N^3; spectrum: (N/2+1) N^2 complex64.  Each byte that a kernel
     must read or write once: positions 12 B/particle (uint32 x3), velocities
     12 B/particle, int64 mass 8 B/cell, float meshes 4 B/cell.  Inside a call
-    the Q stencil reads delta and phi and writes psi = F_g phi + F_q Q, and
-    the next gather reads psi alone; the last stencil launch of a call writes
-    Q and the first gather of a continued call reads phi and Q.
+    the last pass of the solve (with the Q stencil in it) reads the spectrum
+    and delta and writes psi = F_g phi + F_q Q, and the next gather reads psi
+    alone; the last such launch of a call writes phi and Q and the first
+    gather of a continued call reads them.
     """
     cells = n ** 3
     spec = 8 * (n // 2 + 1) * n * n
@@ -57,8 +58,9 @@ def alg_bytes(n: int, npart: int, steps: int = 20) -> dict:
         "fft_x_green": 2 * spec,
         "fft_y_inv": 2 * spec,
         "c2r_z": spec + 4 * cells,
-        # delta and phi in, psi out (k - 1 launches); delta in, Q out (one)
-        "qpot": (12 * (k - 1) + 8) * cells // k,
+        # spectrum and delta in, psi out (k - 1 launches) or phi and Q (one)
+        "c2r_q": spec + (8 * (k - 1) + 12) * cells // k,
+        "qpot": 8 * cells,                          # pm_qpot alone: delta in, Q out
         # pos+vel in/out, psi once (phi and Q in the first launch), and the
         # fused deposit of the drifted particles (read+write of the int64
         # mass mesh once)
@@ -281,7 +283,7 @@ def copy_calibration(nbytes=1 << 30, reps=3):
 # writes psi)
 TRAFFIC_KERNEL = {"gather_kick_drift": "k_gather_tiled<{ln}, true, false, 1, true, 0, false>",
                   "deposit": "k_deposit_tiled<{ln}, true>",
-                  "qpot": "k_qpot_tiled<{ln}, true, 2>", "r2c_z": "k_r2c_z<{ln}, 0>",
+                  "c2r_q": "k_c2r_q<{ln}, true, 2>", "r2c_z": "k_r2c_z<{ln}, 0>",
                   "fft_y": "k_fft_y_reg<{ln}, false>", "fft_x_green": "k_fft_x_green_reg<{ln}>",
                   "fft_y_inv": "k_fft_y_reg<{ln}, true>", "c2r_z": "k_c2r_z<{ln}>",
                   "fill_zero": "k_fill_zero16"}
@@ -290,7 +292,7 @@ TRAFFIC_KERNEL = {"gather_kick_drift": "k_gather_tiled<{ln}, true, false, 1, tru
 # the sources each kernel family is built from (its counters go stale when one changes)
 TRAFFIC_SOURCES = {"gather_kick_drift": ("gather.hip", "cic.h", "internal.h"),
                    "deposit": ("deposit.hip", "cic.h", "internal.h"),
-                   "qpot": ("stencil.hip", "internal.h")}
+                   "c2r_q": ("fft.hip", "qpot.h", "internal.h")}
 for _k in ("r2c_z", "fft_y", "fft_x_green", "fft_y_inv", "c2r_z"):
     TRAFFIC_SOURCES[_k] = ("fft.hip", "internal.h")
 TRAFFIC_SOURCES["fill_zero"] = ("deposit.hip", "internal.h")
@@ -591,8 +593,8 @@ def main():
                             "traffic": measured_traffic(dom, n),
                             "alg_bytes": timed[dom]["alg_bytes"]}
         ab = alg_bytes(n, res["np"], args.steps)
-        per_step = ("fill_zero", "r2c_z", "fft_y", "fft_x_green", "fft_y_inv", "c2r_z",
-                    "qpot", "gather_kick_drift")
+        per_step = ("fill_zero", "r2c_z", "fft_y", "fft_x_green", "fft_y_inv", "c2r_q",
+                    "gather_kick_drift")
         step_bytes = sum(ab[k] for k in per_step)
         line["step_alg_bytes"] = step_bytes
         line["step_alg_GBs"] = round(step_bytes / (res["wall_s"] / args.steps) / 1e9, 1)

@@ -196,8 +196,8 @@ pm_status pm_step(pm_ctx* ctx, void* d_pos, float* d_vel, const double* times,
  * differences of Eq. (11)'s mesh sum, E = K + W + U) at every synchronised
  * time of the call.  d_energies: device array of (nsteps + 1) x 4 doubles;
  * row s receives K, W, U, E at times[s] (a = times[s] in a comoving box).
- * The partial sums are formed inside the step's own kernels: the Q stencil
- * adds up delta phi and the squared forward differences per block, the fused
+ * The partial sums are formed inside the step's own kernels: the last pass of
+ * the solve (with the Q stencil) adds up delta phi and the squared forward differences per block, the fused
  * gather splits each merged kick at the synchronised time and adds up |p|^2
  * there; a one-block kernel per row sums the partials in a fixed order, so
  * the rows are deterministic.  With PM_CONTINUE on a context whose fields
@@ -311,12 +311,13 @@ pm_status pm_spline_qforce(pm_ctx* ctx, const void* d_pos, const float* d_q, dou
  * -grad phi interpolated by cloud-in-cell, as the host code's PM does) and
  * takes Q on it with the kernel-gradient force (pm_spline_qforce), with the
  * FP64 near-empty path of the fixed-point form.  Comoving factors as pm_step
- * (Q's kick carries 1/a^3, gravity's 1/a^2).  Unfused: separate deposit,
- * Poisson, Q, force, kick and drift kernels, no merged half-kicks, two extra
- * [3][Np] float arrays in the workspace's particle buffers.  The particle
- * order is the caller's; on a context sorted by pm_sort the deposit runs
- * from the tiles' LDS windows (particles that left their tile since the sort
- * add directly; the result does not depend on it).  Enqueues only;
+ * (Q's kick carries 1/a^3, gravity's 1/a^2), with no merged half-kicks.  The
+ * particle order is the caller's.  On a context sorted by pm_sort the deposit
+ * runs from the tiles' LDS windows (particles that left their tile since the
+ * sort add directly; the density does not depend on it) and, for h <= 5 and
+ * hbar_over_m > 0, one pass over the particles takes both forces, the kicks
+ * and the drift; otherwise these are separate kernels with two [3][Np] float
+ * arrays in the workspace's particle buffers.  Enqueues only;
  * positions and velocities are synchronised on entry and on return.  Leaves
  * no cloud-in-cell field valid (later calls recompute them). */
 pm_status pm_spline_step(pm_ctx* ctx, void* d_pos, float* d_vel, const double* times,

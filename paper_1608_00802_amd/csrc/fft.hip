@@ -14,7 +14,8 @@
 //      happen on one LDS tile.
 //   4. y-pass  (inverse).
 //   5. z-pass  (C2R): pack the Hermitian half-rows into a length-N/2 complex
-//      sequence, inverse FFT, write real rows.
+//      sequence, inverse FFT, write real rows -- or, with the quantum pressure
+//      wanted, go on to the Q stencil from them (k_c2r_q).
 //
 // The y and x passes split each length-N transform into two factors whose
 // short DFTs run in registers, with one exchange through LDS between them

@@ -178,8 +178,7 @@ __global__ void __launch_bounds__(kQBlock, 8) k_qpot_tiled(const float* __restri
   // once the next plane is known to hold a near-empty cell (block-uniform),
   // so its FP64 values do not wait for a full load latency (evolved 256^3
   // box: 119 -> 95 us; it takes the last 2 of the 64 VGPRs that two blocks
-  // per CU allow, hence the launch bound of 8 waves per SIMD; the energy
-  // form keeps its 80 VGPRs and one block per CU rather than spill).
+  // per CU allow, hence the launch bound of 8 waves per SIMD).
   long long mpre[PER];
   bool mpre_ok = false;
   const int cc = (ty + 1) * PZ + tz + 1;
