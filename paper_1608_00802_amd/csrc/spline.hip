@@ -263,10 +263,11 @@ __device__ __forceinline__ void each_lane(bool which, const int i[3], const floa
 // 2^52 (kSplinePiece particles of at most 8 / (pi h^3) < 0.32 each, in 2^-40).
 //
 // What bounds it is the kernel arithmetic (8 to 12 instructions per node) and
-// the LDS adds (11 cycles per wave instruction at scattered addresses): 1.53
+// the LDS adds (11 cycles per wave instruction at scattered addresses): 1.4
 // ms at 256^3 with one particle per cell and h = 3.5, against 3.88 with
-// per-particle spans; 10^6 particles in one object at 128^3, h = 4: 0.33
-// against 0.99 ms.  512 threads per block: 256 take 1.74 ms, 1024 1.56.
+// per-particle spans; 10^6 particles in one object at 128^3, h = 4: 0.20
+// against 0.99 ms.  512 threads per block (1.53 ms with all nodes of the
+// particles out of their tile on the mesh): 256 take 1.74 ms, 1024 1.56.
 constexpr int kSplineBlock = 512;
 constexpr int kSplineGrid = 4096;
 constexpr int kSplineH2Max = 10;   // the widest window: h <= 5
