@@ -373,10 +373,12 @@ typedef struct {
 /* Largest number of steps one pm_batch_step call may take. */
 #define PM_BATCH_MAX_STEPS 256
 /* Flag of pm_batch_step: capture the call's kernels in a HIP graph the first
- * time a call of its shape is made -- shape: the number of listed slots,
- * nsteps, the other flags and whether every listed slot was sorted on entry
- * -- and replay the graph for later calls of the same shape (up to 64 graphs
- * per batch, freed by pm_batch_destroy); the upload of the call's slot list
+ * time a call of its shape is made with these particle arrays -- shape: the
+ * number of listed slots, nsteps, the other flags and whether every listed
+ * slot was sorted on entry -- and replay the graph for later calls of the
+ * same shape with the same d_pos and d_vel (up to 64 graphs per batch, freed
+ * by pm_batch_destroy; the call that would make one more waits for the stream
+ * and drops them all first); the upload of the call's slot list
  * and kick/drift table precedes the graph on the stream as in an uncaptured
  * call.
  * The slot identities and the time-step factors are data of the uploaded

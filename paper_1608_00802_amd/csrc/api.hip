@@ -120,8 +120,9 @@ struct pm_batch {
   hipEvent_t h_done[2] = {nullptr, nullptr};
   int h_next = 0;
   // PM_BATCH_GRAPH: executable graphs of the kernels of captured calls, by
-  // shape (listed slots, steps, flags, every listed slot sorted on entry)
-  std::map<std::tuple<int, int, int, int>, hipGraphExec_t> graphs;
+  // shape (listed slots, steps, flags, every listed slot sorted on entry) and
+  // particle arrays (their addresses are arguments of the captured launches)
+  std::map<std::tuple<int, int, int, int, const void*, const void*>, hipGraphExec_t> graphs;
 };
 
 namespace {
@@ -1492,9 +1493,10 @@ pm_status pm_batch_step(pm_batch* b, void* d_pos, float* d_vel, int32_t nactive,
   };
   // Every kernel of the call, in stream order after the upload of its slot
   // list and constant table.  Every launch argument depends only on the
-  // call's shape (the slot identities and the factors are read from the
-  // uploaded table), so a captured graph of one call's kernels serves every
-  // later call of the same shape.  The upload itself stays outside the graph:
+  // call's shape and particle arrays (the slot identities and the factors are
+  // read from the uploaded table), so a captured graph of one call's kernels
+  // serves every later call of the same shape on the same arrays.  The upload
+  // itself stays outside the graph:
   // an event recorded in a capturing stream is not replayed, and the host
   // must know when each staging buffer's copy is done.
   auto enqueue = [&]() -> pm_status {
@@ -1548,10 +1550,12 @@ pm_status pm_batch_step(pm_batch* b, void* d_pos, float* d_vel, int32_t nactive,
   if (!use_graph) {
     PM_TRY(enqueue());
   } else {
-    const auto key = std::make_tuple((int)nactive, (int)nsteps, (int)flags, (int)all_sorted);
+    const auto key = std::make_tuple((int)nactive, (int)nsteps, (int)flags, (int)all_sorted,
+                                     (const void*)d_pos, (const void*)d_vel);
     auto it = b->graphs.find(key);
     if (it == b->graphs.end()) {
       if (b->graphs.size() >= 64) {
+        PM_TRY(dev(hipStreamSynchronize(c->stream)));   // none of them is running
         for (auto& g : b->graphs) (void)hipGraphExecDestroy(g.second);
         b->graphs.clear();
       }

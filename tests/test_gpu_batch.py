@@ -207,3 +207,36 @@ def test_batch_graph_replay_equals_eager(pm, gpu, flags_sort):
     if b0.stream.cuda_stream == 0:
         with pytest.raises(pm.PMError):
             b0.step([0], [_sched(0.01, 2)], pm.PM_BATCH_GRAPH)
+
+
+def test_batch_graph_follows_its_particle_arrays(pm, gpu):
+    """Replayed calls of one shape on different particle arrays step the arrays
+    they are given (bitwise the uncaptured calls) and leave the others alone."""
+    import torch
+    states = _states()[:2]
+    box, m, _, a0 = RUNS[0]
+    lp, hm = _params(pm, box, m)
+    stream = torch.cuda.Stream(gpu)
+    times = [_sched(a0, 3)]
+    with torch.cuda.stream(stream):
+        b = pm.PMBatch(lp, 1, device=gpu, stream=stream)
+        start = [(torch.from_numpy(st.pos_fixed.view(np.int32).copy()).to(gpu),
+                  torch.from_numpy(st.vel32.copy()).to(gpu)) for st in states]
+        b.load(0, *start[0], box, hm)
+
+        def arrays():
+            return [(p.clone()[None], v.clone()[None]) for p, v in start]
+
+        eager, replayed = arrays(), arrays()
+        for flag, sets in ((0, eager), (pm.PM_BATCH_GRAPH, replayed)):
+            for pos, vel in (sets[0], sets[1], sets[0], sets[1]):
+                other = sets[1] if pos is sets[0][0] else sets[0]
+                before = [t.clone() for t in other]
+                b.pos, b.vel = pos, vel
+                b.step([0], times, flag)
+                torch.cuda.synchronize()
+                assert all(torch.equal(x, y) for x, y in zip(before, other))
+        for (p, v), (pr, vr) in zip(eager, replayed):
+            assert torch.equal(p, pr) and torch.equal(v, vr)
+        assert not torch.equal(eager[0][0], start[0][0][None])
+        b.close()
