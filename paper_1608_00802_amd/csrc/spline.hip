@@ -411,6 +411,8 @@ __device__ __forceinline__ void force_rows(const Folded<H2>& fo, At&& at, float 
   g[2] = gz;
 }
 
+// Any particle order, any h: a lane walks its own spans and loads Q only
+// inside the support (r = 0 adds nothing).
 __global__ void __launch_bounds__(kBlock) k_spline_qforce(const uint32_t* __restrict__ pos,
                                                           int64_t np, SplinePos sp,
                                                           const float* __restrict__ qmesh, float h,
@@ -422,6 +424,7 @@ __global__ void __launch_bounds__(kBlock) k_spline_qforce(const uint32_t* __rest
     float f[3], g[3] = {0.0f, 0.0f, 0.0f};
     load_cell(sp, pos, np, p, i, f);
     each_node(sp.logn, i, f, h, inv_h, lo, hi, [&](int node, float x, float y, float z, float s) {
+      if (s > 1.0f || s == 0.0f) return;
       const float v = qmesh[node] * spline_g<true>(s);
       g[0] = fmaf(v, x, g[0]);
       g[1] = fmaf(v, y, g[1]);
@@ -432,7 +435,8 @@ __global__ void __launch_bounds__(kBlock) k_spline_qforce(const uint32_t* __rest
   }
 }
 
-// The same nodes at compile time, Q read from the mesh (any particle order).
+// The nodes of the reach at compile time, Q read from the mesh (any particle
+// order).
 template <int H2>
 __global__ void __launch_bounds__(kBlock) k_spline_qforce_fixed_reach(
     const uint32_t* __restrict__ pos, int64_t np, SplinePos sp, const float* __restrict__ qmesh,
@@ -629,6 +633,21 @@ SplinePos spline_pos(bool fixed, int logn) {
   return sp;
 }
 
+// Up to this many particles, too few to hide the latency of the own spans'
+// loops, a force in any order takes all nodes of the reach (h up to 5 cells):
+// 32768 at 32^3 20 to 29 us, own spans 55 to 63.  Beyond, the loads bound it
+// and the own spans have fewer: 2^17 at 64^3, h = 3.5, in lattice order,
+// random order and clumps 57, 98 and 96 us (reach 35, 112, 112; h = 3.01: 39,
+// 66, 65 against 35, 112, 112), 128^3 particles 421, 1928, 1623 against 544,
+// 2802, 2293.
+constexpr int64_t kReachMax = 1 << 16;
+// So few in tiles of more than one pass of a block are too few blocks: 32768
+// at 32^3 (16 tiles) 49 us in lattice order and 66 in clumps, 20 and 22 by the
+// reach; within one pass the tiles win (64^3: 18 against 25).
+constexpr bool few_blocks(int64_t np, int tiles) {
+  return np <= kReachMax && np > (int64_t)kSplineBlock * tiles;
+}
+
 // The reach class of h, in half cells (0: wider than the fixed classes).
 int spline_class(float h) {
   const int h2 = (int)ceilf(2.0f * h);
@@ -696,7 +715,7 @@ hipError_t launch_spline_qforce(bool fixed, int logn, const void* pos, int64_t n
   const uint32_t* words = static_cast<const uint32_t*>(pos);
   const float coef = spline_force_coef(h);
   const int h2 = spline_class(h);
-  if (tm && h2) {
+  if (tm && h2 && !few_blocks(np, tm->tiles)) {
     const dim3 g(piece_grid(np, tm->tiles));
 #define T_(H2)                                                                                  \
   {                                                                                             \
@@ -710,7 +729,7 @@ hipError_t launch_spline_qforce(bool fixed, int logn, const void* pos, int64_t n
   }
     FDM_REACH_SWITCH(h2, T_)
 #undef T_
-  } else if (h2) {
+  } else if (h2 && np <= kReachMax) {
 #define L_(H2)                                                                              \
   hipLaunchKernelGGL((k_spline_qforce_fixed_reach<H2>), dim3(spline_grid(np)), dim3(kBlock), 0, \
                      s, words, np, sp, q, 1.0f / h, coef, acc)

@@ -1,0 +1,98 @@
+"""The kernels that a spline call can take, by order, size and support: the
+same results on each, and none that costs a multiple of another."""
+
+import numpy as np
+import pytest
+
+from synth import quantize_state
+
+from gpu_helpers import to_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def pm(gpu):
+    import paper_1608_00802_amd as pm_mod
+    pm_mod.load_library()
+    return pm_mod
+
+
+def _random(n, npart, seed):
+    rng = np.random.default_rng(seed)
+    return quantize_state(rng.random((npart, 3)) * n, 0.05 * rng.standard_normal((npart, 3)), n, {})
+
+
+def _lattice(n):
+    """One particle per cell, in the mesh's order, moved by 0.3 cells (rms)."""
+    rng = np.random.default_rng(n)
+    i = np.stack(np.meshgrid(*[np.arange(n)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    return quantize_state((i + 0.3 * rng.standard_normal(i.shape)) % n, np.zeros(i.shape), n, {})
+
+
+def _us(fn, reps=5):
+    """Shortest GPU time of one call, in us."""
+    import torch
+    fn()
+    best = float("inf")
+    for _ in range(reps):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        fn()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3)
+    return best
+
+
+def _force_bound(x, q, n, h):
+    """The force in FP64, and the bound of sums of fewer than 1500 terms in
+    any order with a few roundings in each."""
+    i = np.floor(x).astype(np.int64)
+    reach = np.arange(-int(h), int(h) + 2)
+    o = np.stack(np.meshgrid(reach, reach, reach, indexing="ij"), -1).reshape(-1, 3)
+    d = o[None] - (x - i)[:, None]
+    at = (i[:, None] + o[None]) % n
+    r = np.sqrt((d * d).sum(-1))
+    s = r / h
+    slope = np.where(s <= 0.5, -12 * s + 18 * s ** 2, -6 * np.clip(1 - s, 0, None) ** 2)
+    term = (q[(at[..., 0] * n + at[..., 1]) * n + at[..., 2]] * 8 / (np.pi * h ** 4) * slope
+            / np.maximum(r, 1e-30))[..., None] * d
+    return term.sum(1), 1500 * 2.0 ** -24 * np.abs(term).sum(1) + 1e-12
+
+
+@pytest.mark.parametrize("h", [2.0, 3.01, 5.0])
+@pytest.mark.parametrize("npart", [300, (1 << 16) - 1, (1 << 16) + 1])
+def test_force_on_every_route(pm, gpu, npart, h):
+    """Below and above the counts at which a force changes its kernel, in the
+    caller's order and sorted, against sums in FP64 (of 700 particles)."""
+    import torch
+    n = 32
+    st = _random(n, npart, npart)
+    q = np.random.default_rng(1).standard_normal(n ** 3).astype(np.float32)
+    pick = np.random.default_rng(2).permutation(npart)[:700]
+    ref, bound = _force_bound(st.pos[pick], q, n, h)
+    for order in (False, True):
+        ctx = pm.PMContext(pm.make_params(n, npart, float(n), hbar_over_m=1.0), device=gpu)
+        pos, vel = to_device(st, gpu)
+        ids = torch.arange(npart, dtype=torch.int32, device=gpu)
+        if order:
+            ctx.sort(pos, vel, ids)
+        acc = torch.empty((3, npart), dtype=torch.float32, device=gpu)
+        ctx.spline_qforce(pos, torch.from_numpy(q).to(gpu), acc, h)
+        back = torch.empty_like(acc)
+        back[:, ids.long()] = acc
+        g = back.cpu().numpy().T[pick].astype(np.float64)
+        assert np.all(np.abs(g - ref) <= bound)
+
+
+def test_unsorted_force_loads_its_own_support(pm, gpu):
+    """Many particles in random order: the cost follows the support, not the
+    half-cell class above it (114 of 180 nodes at h = 3.01 and 3.5)."""
+    import torch
+    n, npart = 128, 1 << 20
+    pos, _ = to_device(_random(n, npart, 3), gpu)
+    ctx = pm.PMContext(pm.make_params(n, npart, float(n), hbar_over_m=1.0), device=gpu)
+    q, acc = torch.randn(n ** 3, device=gpu), torch.empty((3, npart), device=gpu)
+    narrow, wide = (_us(lambda: ctx.spline_qforce(pos, q, acc, h)) for h in (3.01, 3.5))
+    assert narrow <= 0.85 * wide
