@@ -312,9 +312,9 @@ pm_status pm_spline_qforce(pm_ctx* ctx, const void* d_pos, const float* d_q, dou
  * takes Q on it with the kernel-gradient force (pm_spline_qforce), with the
  * FP64 near-empty path of the fixed-point form.  Comoving factors as pm_step
  * (Q's kick carries 1/a^3, gravity's 1/a^2), with no merged half-kicks.  The
- * particle order is the caller's.  On a context sorted by pm_sort the deposit
- * runs from the tiles' LDS windows (particles that left their tile since the
- * sort add directly; the density does not depend on it) and, for h <= 5 and
+ * particle order is the caller's.  On a context sorted by pm_sort, for h <= 5
+ * and unless its tiles are many and nearly empty, the deposit runs from the
+ * tiles' LDS windows (the density does not depend on it) and, for
  * hbar_over_m > 0, one pass over the particles takes both forces, the kicks
  * and the drift; otherwise these are separate kernels with two [3][Np] float
  * arrays in the workspace's particle buffers.  Enqueues only;

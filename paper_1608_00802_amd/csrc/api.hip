@@ -1182,9 +1182,9 @@ pm_status pm_spline_step(pm_ctx* c, void* d_pos, float* d_vel, const double* tim
   // gradient of Q, [3][Np] floats each in the particle copy buffers
   float* gphi = reinterpret_cast<float*>(c->pos_tmp);
   float* gq = c->vel_tmp;
-  // On a sorted context with quantum pressure both forces, the kicks and the
-  // drift are one pass over the particles.
-  const bool fused = c->sorted && c->has_q && spline_step_fused((float)h);
+  // On a sorted context with quantum pressure (and enough particles per tile)
+  // both forces, the kicks and the drift are one pass over the particles.
+  const bool fused = c->sorted && c->has_q && spline_step_fused((float)h, c->np, c->tiles);
   auto fields = [&]() -> pm_status {
     PM_TRY(run_spline_density(c, d_pos, h));
     return c->has_q ? run_poisson_q(c, kSrcMass64, kOutQ) : run_poisson(c, kSrcMass64, c->mass);

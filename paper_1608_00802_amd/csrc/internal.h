@@ -342,13 +342,13 @@ hipError_t launch_spline_qforce(bool fixed, int logn, const void* pos, int64_t n
 // One pass of the spline step over the particles of a sorted context: both
 // forces at the current positions, the closing half-kick of the previous step
 // (if close), the opening half-kick and the drift of the next (if open).  For
-// the supports that spline_step_fused accepts.
+// the supports and particle counts that spline_step_fused accepts.
 struct SplineKicks {
   float close_g, close_q, open_g, open_q;
   double drift;
   bool close, open;
 };
-bool spline_step_fused(float h);
+bool spline_step_fused(float h, int64_t np, int tiles);
 hipError_t launch_spline_push(bool fixed, int logn, void* pos, float* vel, int64_t np,
                               const float* phi, const float* q, float h, const TileMap& tm,
                               const SplineKicks& k, hipStream_t s);

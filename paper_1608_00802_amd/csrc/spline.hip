@@ -641,6 +641,21 @@ SplinePos spline_pos(bool fixed, int logn) {
 // 66, 65 against 35, 112, 112), 128^3 particles 421, 1928, 1623 against 544,
 // 2802, 2293.
 constexpr int64_t kReachMax = 1 << 16;
+// Tiles in the order of a sort.  Each costs its window, whatever it holds; up
+// to four per CU that is one round of blocks, beyond it takes enough particles
+// to share it.  At 256^3 (8192 tiles; lattice and random order, in us):
+//   force, h = 3.5:   2^17 particles 163, 164 (spans 106, 129),
+//                     2^18 162, 162 (173, 214), 2^19 172, 175 (298, 571)
+//   force, h = 2:     2^18 78, 78 (47, 53), 2^19 80, 80 (76, 128)
+//   density, h = 5:   2^14 828, 943 (direct 498, 504), 2^16 1050 (1530, 1580)
+//   two steps, h = 3.5: 2^15 2785, 2764 as one pass, 1815, 1851 in separate ones
+bool tiles_pay(int64_t np, int tiles, int per_tile) {
+  return tiles <= 1024 || np >= (int64_t)per_tile * tiles;
+}
+bool force_tiles_pay(int64_t np, int tiles, int h2) {
+  return tiles_pay(np, tiles, h2 <= 5 ? 64 : 32);
+}
+bool deposit_tiles_pay(int64_t np, int tiles) { return tiles_pay(np, tiles, 4); }
 // So few in tiles of more than one pass of a block are too few blocks: 32768
 // at 32^3 (16 tiles) 49 us in lattice order and 66 in clumps, 20 and 22 by the
 // reach; within one pass the tiles win (64^3: 18 against 25).
@@ -687,7 +702,7 @@ hipError_t launch_spline_deposit(bool fixed, int logn, const void* pos, int64_t 
   const uint32_t* words = static_cast<const uint32_t*>(pos);
   const double unit = ldexp(16.0 / (M_PI * (double)h * h * h), kMassShift);
   const int h2 = spline_class(h);
-  if (tm && h2) {
+  if (tm && h2 && deposit_tiles_pay(np, tm->tiles)) {
     const dim3 g(piece_grid(np, tm->tiles));
 #define T_(H2)                                                                                   \
   {                                                                                              \
@@ -715,7 +730,7 @@ hipError_t launch_spline_qforce(bool fixed, int logn, const void* pos, int64_t n
   const uint32_t* words = static_cast<const uint32_t*>(pos);
   const float coef = spline_force_coef(h);
   const int h2 = spline_class(h);
-  if (tm && h2 && !few_blocks(np, tm->tiles)) {
+  if (tm && h2 && !few_blocks(np, tm->tiles) && force_tiles_pay(np, tm->tiles, h2)) {
     const dim3 g(piece_grid(np, tm->tiles));
 #define T_(H2)                                                                                  \
   {                                                                                             \
@@ -758,7 +773,10 @@ hipError_t launch_spline_drift(bool fixed, int logn, void* pos, const float* vel
   return hipGetLastError();
 }
 
-bool spline_step_fused(float h) { return spline_class(h) != 0; }
+bool spline_step_fused(float h, int64_t np, int tiles) {
+  const int h2 = spline_class(h);
+  return h2 && force_tiles_pay(np, tiles, h2);
+}
 
 hipError_t launch_spline_push(bool fixed, int logn, void* pos, float* vel, int64_t np,
                               const float* phi, const float* q, float h, const TileMap& tm,

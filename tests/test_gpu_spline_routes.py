@@ -96,3 +96,38 @@ def test_unsorted_force_loads_its_own_support(pm, gpu):
     q, acc = torch.randn(n ** 3, device=gpu), torch.empty((3, npart), device=gpu)
     narrow, wide = (_us(lambda: ctx.spline_qforce(pos, q, acc, h)) for h in (3.01, 3.5))
     assert narrow <= 0.85 * wide
+
+
+@pytest.mark.parametrize("h", [2.0, 3.5, 5.0])
+@pytest.mark.parametrize("npart", [8192 * 4 - 1, 8192 * 4, 8192 * 32 - 1, 8192 * 32])
+def test_sparse_sorted_context(pm, gpu, npart, h):
+    """8192 tiles (256^3) on both sides of the counts from which their windows
+    are used: the density bitwise the unsorted one, the force the same sums
+    (bound: each sum's 300 terms rounded in another order), the step's route
+    read from its kernels."""
+    import torch
+    n = 256
+    st = _random(n, npart, npart)
+    q = torch.randn(n ** 3, generator=torch.Generator(device=gpu).manual_seed(1), device=gpu)
+    out = []
+    for order in (False, True):
+        ctx = pm.PMContext(pm.make_params(n, npart, float(n), hbar_over_m=1e-4), device=gpu)
+        pos, vel = to_device(st, gpu)
+        ids = torch.arange(npart, dtype=torch.int32, device=gpu)
+        if order:
+            ctx.sort(pos, vel, ids)
+        delta, acc = torch.empty(n ** 3, device=gpu), torch.empty((3, npart), device=gpu)
+        ctx.spline_density(pos, delta, h)
+        ctx.spline_qforce(pos, q, acc, h)
+        ctx.timing(True)
+        ctx.spline_step(pos, vel, [0.0, 0.01], h)
+        kernels = ctx.timing_read()
+        back, v = torch.empty_like(acc), torch.empty_like(vel)
+        back[:, ids.long()], v[:, ids.long()] = acc, vel
+        out.append((delta, back.double(), v.double(), "force" in kernels))
+    assert torch.equal(out[0][0], out[1][0])
+    scale = float(out[0][1].abs().max())
+    assert float((out[0][1] - out[1][1]).abs().max()) <= 300 * 2.0 ** -24 * 8 * scale
+    kick = float((out[0][2] - torch.from_numpy(st.vel32.astype(np.float64)).to(gpu)).abs().max())
+    assert float((out[0][2] - out[1][2]).abs().max()) <= 2.0 ** -16 * kick + 2.0 ** -22
+    assert out[0][3] and out[1][3] == (npart < 8192 * (64 if h < 2.5 else 32))
