@@ -295,7 +295,9 @@ pm_status pm_power_spectrum(pm_ctx* ctx, const void* d_pos, int32_t nbins,
  * every particle by the kernel gradient, Eq. (14): a_i = sum_j Q_j
  * grad W(x_j - q_i) (cell units, dx = 1), with the sign that makes it
  * -grad Q, i.e. minus the particle derivative of the discrete K_rho of
- * Eq. (11) whose node derivative is Q.  d_q is float [N^3] as from pm_qpot.
+ * Eq. (11) whose node derivative is Q.  d_q is float [N^3] as from pm_qpot;
+ * a particle reads nothing from nodes beyond h (or from the node it sits on),
+ * so a value there that is not finite does not reach it.
  *
  * Both enqueue only.  PM_EINVAL for null pointers or h outside
  * [2, 16] (below two cells the lattice sum of W, a particle's deposited

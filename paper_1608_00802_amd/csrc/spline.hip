@@ -14,6 +14,7 @@
 // formed from it by the exact subtraction of the mean (the forward z pass),
 // and near-empty nodes keep their full relative precision (no sum starting
 // from -1), which is what the FP64 path of the Q stencil reads there.
+#include <cfloat>
 #include <utility>
 
 #include "cic.h"
@@ -387,7 +388,10 @@ __global__ void __launch_bounds__(kSplineBlock, 4) k_spline_deposit_tiled(
 }
 
 // Force of one particle from its rows: at(a, b) gives an accessor of Q along
-// the row, at offsets c from the particle's cell.
+// the row, at offsets c from the particle's cell.  Nodes of the reach beyond
+// the support and the node that the particle sits on enter as Q times zero: a
+// force that is not finite has to be taken again from its own spans, where
+// they stay out (checking each product instead costs a tenth of the kernel).
 template <int H2, class At>
 __device__ __forceinline__ void force_rows(const Folded<H2>& fo, At&& at, float g[3]) {
   using Rc = Reach<H2>;
@@ -411,8 +415,29 @@ __device__ __forceinline__ void force_rows(const Folded<H2>& fo, At&& at, float 
   g[2] = gz;
 }
 
-// Any particle order, any h: a lane walks its own spans and loads Q only
+// Force of one particle from its own spans, Q read from the mesh and only
 // inside the support (r = 0 adds nothing).
+__device__ __forceinline__ void own_force(int logn, const int i[3], const float f[3], float h,
+                                          float inv_h, int lo, int hi,
+                                          const float* __restrict__ qmesh, float g[3]) {
+  g[0] = g[1] = g[2] = 0.0f;
+  each_node(logn, i, f, h, inv_h, lo, hi, [&](int node, float x, float y, float z, float s) {
+    if (s > 1.0f || s == 0.0f) return;
+    const float v = qmesh[node] * spline_g<true>(s);
+    g[0] = fmaf(v, x, g[0]);
+    g[1] = fmaf(v, y, g[1]);
+    g[2] = fmaf(v, z, g[2]);
+  });
+}
+
+// (The sums are made opaque first: seen through, the check has the compiler
+// keep the operands of every term, thousands of bytes of scratch per lane.)
+__device__ __forceinline__ bool all_finite(float (&g)[3]) {
+  asm volatile("" : "+v"(g[0]), "+v"(g[1]), "+v"(g[2]));
+  return fabsf(g[0]) <= FLT_MAX && fabsf(g[1]) <= FLT_MAX && fabsf(g[2]) <= FLT_MAX;
+}
+
+// Any particle order, any h.
 __global__ void __launch_bounds__(kBlock) k_spline_qforce(const uint32_t* __restrict__ pos,
                                                           int64_t np, SplinePos sp,
                                                           const float* __restrict__ qmesh, float h,
@@ -421,15 +446,9 @@ __global__ void __launch_bounds__(kBlock) k_spline_qforce(const uint32_t* __rest
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < np; p += stride) {
     int i[3];
-    float f[3], g[3] = {0.0f, 0.0f, 0.0f};
+    float f[3], g[3];
     load_cell(sp, pos, np, p, i, f);
-    each_node(sp.logn, i, f, h, inv_h, lo, hi, [&](int node, float x, float y, float z, float s) {
-      if (s > 1.0f || s == 0.0f) return;
-      const float v = qmesh[node] * spline_g<true>(s);
-      g[0] = fmaf(v, x, g[0]);
-      g[1] = fmaf(v, y, g[1]);
-      g[2] = fmaf(v, z, g[2]);
-    });
+    own_force(sp.logn, i, f, h, inv_h, lo, hi, qmesh, g);
 #pragma unroll
     for (int d = 0; d < 3; ++d) acc[d * np + p] = coef * g[d];
   }
@@ -440,7 +459,7 @@ __global__ void __launch_bounds__(kBlock) k_spline_qforce(const uint32_t* __rest
 template <int H2>
 __global__ void __launch_bounds__(kBlock) k_spline_qforce_fixed_reach(
     const uint32_t* __restrict__ pos, int64_t np, SplinePos sp, const float* __restrict__ qmesh,
-    float inv_h, float coef, float* __restrict__ acc) {
+    float h, float inv_h, float coef, float* __restrict__ acc) {
   using Rc = Reach<H2>;
   const int mask = (1 << sp.logn) - 1;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -464,6 +483,7 @@ __global__ void __launch_bounds__(kBlock) k_spline_qforce_fixed_reach(
                                                (row | zo[c + Rc::R]));
       };
     }, g);
+    if (!all_finite(g)) own_force(sp.logn, i, f, h, inv_h, -Rc::R, Rc::R + 1, qmesh, g);
 #pragma unroll
     for (int d = 0; d < 3; ++d) acc[d * np + p] = coef * g[d];
   }
@@ -508,7 +528,7 @@ __device__ __forceinline__ uint32_t spline_drift(const SplinePos& sp, uint32_t r
 template <int H2, bool STEP>
 __global__ void __launch_bounds__(kSplineBlock, H2 <= 7 && !STEP ? 8 : 5) k_spline_qforce_tiled(
     uint32_t* __restrict__ pos, int64_t np, SplinePos sp, TileMap tm,
-    const float* __restrict__ qmesh, float inv_h, float coef, float* __restrict__ acc,
+    const float* __restrict__ qmesh, float h, float inv_h, float coef, float* __restrict__ acc,
     SplineStep st) {
   using Tile = SplineTile<H2>;
   extern __shared__ float qwin[];
@@ -554,11 +574,14 @@ __global__ void __launch_bounds__(kSplineBlock, H2 <= 7 && !STEP ? 8 : 5) k_spli
           const float* row = qwin + (base + a.value * sx + bb.value * sy);
           return [row](int c) { return row[c + Reach<H2>::R]; };
         }, g);
+        if (!all_finite(g))
+          own_force(sp.logn, i, f, h, inv_h, -Reach<H2>::R, Reach<H2>::R + 1, qmesh, g);
       }
       each_lane(at < 0, i, f, [&](int lane, const int iu[3], const float fu[3]) {
         float w[3] = {0.0f, 0.0f, 0.0f};
         each_node_wave<H2>(sp.logn, iu, fu, inv_h,
                            [&](int node, float x, float y, float z, float s) {
+          if (s > 1.0f || s == 0.0f) return;
           const float t = qmesh[node] * spline_g<true>(s);
           w[0] = fmaf(t, x, w[0]);
           w[1] = fmaf(t, y, w[1]);
@@ -739,7 +762,7 @@ hipError_t launch_spline_qforce(bool fixed, int logn, const void* pos, int64_t n
         allow_lds(reinterpret_cast<const void*>(&k_spline_qforce_tiled<H2, false>), lds);       \
     if (e != hipSuccess) return e;                                                              \
     hipLaunchKernelGGL((k_spline_qforce_tiled<H2, false>), g, dim3(kSplineBlock), lds, s,       \
-                       const_cast<uint32_t*>(words), np, sp, *tm, q, 1.0f / h, coef, acc,       \
+                       const_cast<uint32_t*>(words), np, sp, *tm, q, h, 1.0f / h, coef, acc,    \
                        SplineStep());                                                           \
   }
     FDM_REACH_SWITCH(h2, T_)
@@ -747,7 +770,7 @@ hipError_t launch_spline_qforce(bool fixed, int logn, const void* pos, int64_t n
   } else if (h2 && np <= kReachMax) {
 #define L_(H2)                                                                              \
   hipLaunchKernelGGL((k_spline_qforce_fixed_reach<H2>), dim3(spline_grid(np)), dim3(kBlock), 0, \
-                     s, words, np, sp, q, 1.0f / h, coef, acc)
+                     s, words, np, sp, q, h, 1.0f / h, coef, acc)
     FDM_REACH_SWITCH(h2, L_)
 #undef L_
   } else {
@@ -793,7 +816,7 @@ hipError_t launch_spline_push(bool fixed, int logn, void* pos, float* vel, int64
         allow_lds(reinterpret_cast<const void*>(&k_spline_qforce_tiled<H2, true>), lds);        \
     if (e != hipSuccess) return e;                                                              \
     hipLaunchKernelGGL((k_spline_qforce_tiled<H2, true>), g, dim3(kSplineBlock), lds, s,        \
-                       static_cast<uint32_t*>(pos), np, sp, tm, q, 1.0f / h, coef, nullptr, st); \
+                       static_cast<uint32_t*>(pos), np, sp, tm, q, h, 1.0f / h, coef, nullptr, st); \
   }
   FDM_REACH_SWITCH(spline_class(h), T_)
 #undef T_

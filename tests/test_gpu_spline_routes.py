@@ -131,3 +131,49 @@ def test_sparse_sorted_context(pm, gpu, npart, h):
     kick = float((out[0][2] - torch.from_numpy(st.vel32.astype(np.float64)).to(gpu)).abs().max())
     assert float((out[0][2] - out[1][2]).abs().max()) <= 2.0 ** -16 * kick + 2.0 ** -22
     assert out[0][3] and out[1][3] == (npart < 8192 * (64 if h < 2.5 else 32))
+
+
+@pytest.mark.parametrize("h", [2.0, 3.01, 5.0, 5.3])
+@pytest.mark.parametrize("npart,order", [(300, "none"), (70001, "none"), (300, "sorted"),
+                                         (70001, "sorted"), (70001, "foreign")])
+def test_force_ignores_what_lies_beyond_the_support(pm, gpu, npart, order, h):
+    """Values of Q that are not finite, outside a particle's support or on the
+    node it sits on: its force is the one with zeros there, in FP64."""
+    import torch
+    n = 32
+    rng = np.random.default_rng(npart)
+    x = rng.random((npart, 3)) * n
+    x[: npart // 3] = np.floor(x[: npart // 3])     # on a node
+    st = quantize_state(x, np.zeros((npart, 3)), n, {})
+    bad = rng.random(n ** 3) < (0.005 if h < 4.0 else 0.001)
+    q = rng.standard_normal(n ** 3).astype(np.float32)
+    zero = np.where(bad, 0.0, q).astype(np.float32)
+    q[bad] = rng.choice(np.float32([np.inf, -np.inf, np.nan]), bad.sum())
+    # particles (of 4000) with no bad node within h, up to rounding, but for
+    # the one they sit on
+    pick = rng.permutation(npart)[:4000]
+    i = np.floor(st.pos[pick]).astype(np.int64)
+    reach = np.arange(-int(h), int(h) + 2)
+    clean = np.zeros(npart, dtype=bool)
+    clean[pick] = True
+    for o in np.stack(np.meshgrid(reach, reach, reach, indexing="ij"), -1).reshape(-1, 3):
+        r2 = ((o - (st.pos[pick] - i)) ** 2).sum(1)
+        at = (i + o) % n
+        clean[pick] &= ~((r2 > 0) & (r2 < (h * (1 + 1e-5)) ** 2)
+                         & bad[(at[:, 0] * n + at[:, 1]) * n + at[:, 2]])
+    assert 0.1 < clean[pick].mean() < 0.9
+    ctx = pm.PMContext(pm.make_params(n, npart, float(n), hbar_over_m=1.0), device=gpu)
+    pos, vel = to_device(st, gpu)
+    ids = torch.arange(npart, dtype=torch.int32, device=gpu)
+    if order == "sorted":
+        ctx.sort(pos, vel, ids)
+    elif order == "foreign":
+        other, _ = to_device(_random(n, npart, 8), gpu)
+        ctx.sort(other, vel)
+    acc = torch.empty((3, npart), dtype=torch.float32, device=gpu)
+    ctx.spline_qforce(pos, torch.from_numpy(q).to(gpu), acc, h)
+    back = torch.empty_like(acc)
+    back[:, ids.long()] = acc
+    own = np.flatnonzero(clean)[:1500]
+    ref, bound = _force_bound(st.pos[own], zero, n, h)
+    assert np.all(np.abs(back.cpu().numpy().T[own] - ref) <= bound)
