@@ -678,7 +678,10 @@ bool tiles_pay(int64_t np, int tiles, int per_tile) {
 bool force_tiles_pay(int64_t np, int tiles, int h2) {
   return tiles_pay(np, tiles, h2 <= 5 ? 64 : 32);
 }
-bool deposit_tiles_pay(int64_t np, int tiles) { return tiles_pay(np, tiles, 4); }
+// (clumps, h = 3.5: 2^14 in tiles 211, direct 260)
+bool deposit_tiles_pay(int64_t np, int tiles, int h2) {
+  return h2 < kSplineH2Max || tiles_pay(np, tiles, 4);
+}
 // So few in tiles of more than one pass of a block are too few blocks: 32768
 // at 32^3 (16 tiles) 49 us in lattice order and 66 in clumps, 20 and 22 by the
 // reach; within one pass the tiles win (64^3: 18 against 25).
@@ -725,7 +728,7 @@ hipError_t launch_spline_deposit(bool fixed, int logn, const void* pos, int64_t 
   const uint32_t* words = static_cast<const uint32_t*>(pos);
   const double unit = ldexp(16.0 / (M_PI * (double)h * h * h), kMassShift);
   const int h2 = spline_class(h);
-  if (tm && h2 && deposit_tiles_pay(np, tm->tiles)) {
+  if (tm && h2 && deposit_tiles_pay(np, tm->tiles, h2)) {
     const dim3 g(piece_grid(np, tm->tiles));
 #define T_(H2)                                                                                   \
   {                                                                                              \
