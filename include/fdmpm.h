@@ -297,7 +297,10 @@ pm_status pm_power_spectrum(pm_ctx* ctx, const void* d_pos, int32_t nbins,
  * -grad Q, i.e. minus the particle derivative of the discrete K_rho of
  * Eq. (11) whose node derivative is Q.  d_q is float [N^3] as from pm_qpot;
  * a particle reads nothing from nodes beyond h (or from the node it sits on),
- * so a value there that is not finite does not reach it.
+ * so a value there that is not finite does not reach it.  On a context
+ * sorted by pm_sort the force of the sorted particles runs from their tiles;
+ * positions in another order may be given, at a higher cost than on an
+ * unsorted context.
  *
  * Both enqueue only.  PM_EINVAL for null pointers or h outside
  * [2, 16] (below two cells the lattice sum of W, a particle's deposited

@@ -234,6 +234,19 @@ __device__ __forceinline__ void each_node_wave(int logn, const int i[3], const f
     }
   }
 }
+// Whether a lane's particle, far from its tile, is taken by the lane itself:
+// where many of a wave are, the positions are not those that were sorted (a
+// second state on a sorted context, say), and one after the other they would
+// take a wave each.  Those near their tile, as after some steps without a
+// sort, stay with the waves.  128^3 particles in lattice order on a context
+// that sorted others, h = 3.5: force 3080 -> 790 us (unsorted 409; the blocks
+// are those of the sort), density 17.5 -> 11.7 ms (unsorted 11.5).  Three
+// cells rms after a sort two steps take 10.5 ms, 30 with the near ones taken
+// by lanes too.
+constexpr int kManyFar = 16;
+__device__ __forceinline__ bool by_lane(bool far) {
+  return far && __popcll(__ballot(far)) > kManyFar;
+}
 // fn(lane, its cell, its fraction) for every lane of the wave with `which`
 // set; the whole wave runs it, the arguments are uniform.
 template <class F>
@@ -282,6 +295,7 @@ __host__ __device__ constexpr int spline_window(int logn) {
 // of it and E - BEFORE behind, on each axis.
 template <int BEFORE, int E>
 struct TileWindow {
+  static constexpr int kNear = 8;
   static constexpr int WX = (1 << kTileLX) + E, WY = (1 << kTileLY) + E;
   int o[3], tz, wz;
   __device__ __forceinline__ TileWindow(int logn, int tile) {
@@ -298,6 +312,13 @@ struct TileWindow {
     const int rx = (i[0] - o[0]) & mask, ry = (i[1] - o[1]) & mask, rz = (i[2] - o[2]) & mask;
     if (rx >= (1 << kTileLX) || ry >= (1 << kTileLY) || rz >= tz) return -1;
     return ((rx + BEFORE) * WY + ry + BEFORE) * wz + rz + BEFORE;
+  }
+  // whether a cell is within kNear of the tile
+  __device__ __forceinline__ bool near(int logn, const int i[3]) const {
+    const int mask = (1 << logn) - 1;
+    return ((i[0] - o[0] + kNear) & mask) < (1 << kTileLX) + 2 * kNear &&
+           ((i[1] - o[1] + kNear) & mask) < (1 << kTileLY) + 2 * kNear &&
+           ((i[2] - o[2] + kNear) & mask) < tz + 2 * kNear;
   }
   // window index of a mesh node, or -1 outside the window
   __device__ __forceinline__ int node(int logn, int n) const {
@@ -328,7 +349,7 @@ __host__ __device__ constexpr int grad_window(int logn) {
 
 template <int H2>
 __global__ void __launch_bounds__(kSplineBlock, 4) k_spline_deposit_tiled(
-    const uint32_t* __restrict__ pos, int64_t np, SplinePos sp, TileMap tm, float inv_h,
+    const uint32_t* __restrict__ pos, int64_t np, SplinePos sp, TileMap tm, float h, float inv_h,
     double unit, unsigned long long* __restrict__ mass) {
   using Rc = Reach<H2>;
   using Tile = SplineTile<H2>;
@@ -366,7 +387,14 @@ __global__ void __launch_bounds__(kSplineBlock, 4) k_spline_deposit_tiled(
           });
         });
       }
-      each_lane(at < 0, i, f, [&](int, const int iu[3], const float fu[3]) {
+      const bool own = by_lane(at < 0 && !tile.near(sp.logn, i));
+      if (own)
+        each_node(sp.logn, i, f, h, inv_h, -Rc::R, Rc::R + 1,
+                  [&](int node, float, float, float, float s) {
+          const unsigned long long v = spline_units(spline_w<true>(s), unit) & kUnitMask;
+          if (v != 0ull) atomicAdd(&mass[node], v);
+        });
+      each_lane(at < 0 && !own, i, f, [&](int, const int iu[3], const float fu[3]) {
         each_node_wave<H2>(sp.logn, iu, fu, inv_h, [&](int node, float, float, float, float s) {
           const unsigned long long v = spline_units(spline_w<true>(s), unit) & kUnitMask;
           const int w = tile.node(sp.logn, node);
@@ -565,6 +593,8 @@ __global__ void __launch_bounds__(kSplineBlock, H2 <= 7 && !STEP ? 8 : 5) k_spli
           for (int d = 0; d < 3; ++d) v[d] = st.vel[d * np + p + threadIdx.x];
         }
       }
+      const bool lane_own = by_lane(at < 0 && !tile.near(sp.logn, i));
+      bool own = lane_own;
       if (valid && at >= 0) {
         const Folded<H2> fo(f, inv_h);
         const int px = Tile::WY * tile.wz, py = tile.wz;
@@ -574,10 +604,10 @@ __global__ void __launch_bounds__(kSplineBlock, H2 <= 7 && !STEP ? 8 : 5) k_spli
           const float* row = qwin + (base + a.value * sx + bb.value * sy);
           return [row](int c) { return row[c + Reach<H2>::R]; };
         }, g);
-        if (!all_finite(g))
-          own_force(sp.logn, i, f, h, inv_h, -Reach<H2>::R, Reach<H2>::R + 1, qmesh, g);
+        own = !all_finite(g);
       }
-      each_lane(at < 0, i, f, [&](int lane, const int iu[3], const float fu[3]) {
+      if (own) own_force(sp.logn, i, f, h, inv_h, -Reach<H2>::R, Reach<H2>::R + 1, qmesh, g);
+      each_lane(at < 0 && !lane_own, i, f, [&](int lane, const int iu[3], const float fu[3]) {
         float w[3] = {0.0f, 0.0f, 0.0f};
         each_node_wave<H2>(sp.logn, iu, fu, inv_h,
                            [&](int node, float x, float y, float z, float s) {
@@ -736,7 +766,7 @@ hipError_t launch_spline_deposit(bool fixed, int logn, const void* pos, int64_t 
     const hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_spline_deposit_tiled<H2>), lds); \
     if (e != hipSuccess) return e;                                                               \
     hipLaunchKernelGGL((k_spline_deposit_tiled<H2>), g, dim3(kSplineBlock), lds, s, words, np,   \
-                       sp, *tm, 1.0f / h, unit, mass);                                           \
+                       sp, *tm, h, 1.0f / h, unit, mass);                                        \
   }
     FDM_REACH_SWITCH(h2, T_)
 #undef T_

@@ -177,3 +177,29 @@ def test_force_ignores_what_lies_beyond_the_support(pm, gpu, npart, order, h):
     own = np.flatnonzero(clean)[:1500]
     ref, bound = _force_bound(st.pos[own], zero, n, h)
     assert np.all(np.abs(back.cpu().numpy().T[own] - ref) <= bound)
+
+
+def test_positions_that_were_not_the_sorted_ones(pm, gpu):
+    """A second state, in the mesh's order, on a context that sorted another:
+    the density bitwise and the force the same sums (300 terms rounded in
+    another order) as unsorted, neither at a multiple of its cost."""
+    import torch
+    n, npart, h = 128, 128 ** 3, 3.5
+    lp = pm.make_params(n, npart, float(n), hbar_over_m=1.0)
+    pos, _ = to_device(_lattice(n), gpu)
+    q = torch.randn(n ** 3, generator=torch.Generator(device=gpu).manual_seed(2), device=gpu)
+    out = []
+    for order in (False, True):
+        ctx = pm.PMContext(lp, device=gpu)
+        if order:
+            other, vel = to_device(_random(n, npart, 4), gpu)
+            ctx.sort(other, vel)
+        delta, acc = torch.empty(n ** 3, device=gpu), torch.empty((3, npart), device=gpu)
+        us = [_us(lambda: ctx.spline_density(pos, delta, h), 3),
+              _us(lambda: ctx.spline_qforce(pos, q, acc, h))]
+        out.append((delta, acc.double(), us))
+    assert torch.equal(out[0][0], out[1][0])
+    scale = float(out[0][1].abs().max())
+    assert float((out[0][1] - out[1][1]).abs().max()) <= 300 * 2.0 ** -24 * 8 * scale
+    assert out[1][2][0] <= 1.25 * out[0][2][0]
+    assert out[1][2][1] <= 3.0 * out[0][2][1]
