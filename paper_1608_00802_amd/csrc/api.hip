@@ -83,6 +83,7 @@ struct pm_ctx {
   int q_blocks;
   int k_blocks;
   bool spec_of_delta = false;  // spec holds the forward z pass of the context's delta
+  bool captured = false;       // calls of this context have been captured into a graph
   bool have_delta;   // delta in the workspace was made by pm_deposit
   bool have_phi;
   bool have_q;
@@ -393,6 +394,18 @@ pm_status run_deposit(pm_ctx* c, const void* pos) {
   return run_deposit(c, pos, c->sorted ? &c->tmap : nullptr);
 }
 
+// Notes whether the caller is capturing this context's stream.  A captured
+// call may be replayed at any time, so from then on no call relies on what the
+// host believes to be in the spectrum: a pm_poisson that goes on from the
+// spectrum would transform it again with each replay, and the replay of any
+// captured call overwrites it unseen.  (The null stream cannot be captured.)
+void note_capture(pm_ctx* c) {
+  if (c->captured || !c->stream) return;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  c->captured = hipStreamIsCapturing(c->stream, &st) == hipSuccess &&
+                st != hipStreamCaptureStatusNone;
+}
+
 // Forward z-pass from the context's mass mesh (or from a given delta),
 // remaining passes, potential into c->phi.
 // (in null: the forward z pass of the context's delta is in spec already, as
@@ -495,6 +508,7 @@ pm_status copy_out(pm_ctx* c, float* dst, const float* own, const float* written
 // delta from the mass mesh of the positions just deposited, through the
 // forward z pass, whose spectrum pm_poisson can go on from.
 pm_status form_delta(pm_ctx* c, int src, float* d_delta) {
+  note_capture(c);
   c->spec_of_delta = false;
   float* too = second_output(d_delta, c->delta);
   PM_TRY(timed(c, kcR2C, [&] {
@@ -505,7 +519,7 @@ pm_status form_delta(pm_ctx* c, int src, float* d_delta) {
   c->have_phi = false;
   c->fields_at_pos = false;
   PM_TRY(copy_out(c, d_delta, c->delta, too));
-  c->spec_of_delta = true;
+  c->spec_of_delta = !c->captured;
   return PM_OK;
 }
 
@@ -649,12 +663,14 @@ pm_status pm_deposit(pm_ctx* c, const void* d_pos, float* d_delta) {
 
 pm_status pm_poisson(pm_ctx* c, const float* d_delta, float* d_phi) {
   if (!c) return PM_EINVAL;
+  note_capture(c);
   float* too = second_output(d_phi, c->phi);
   if (d_delta) {
     PM_TRY(run_poisson(c, kSrcDelta, d_delta, too));
   } else {
     if (!c->have_delta) return PM_ESTATE;
-    PM_TRY(run_poisson(c, kSrcDelta, c->spec_of_delta ? nullptr : c->delta, too));
+    const bool go_on = c->spec_of_delta && !c->captured;
+    PM_TRY(run_poisson(c, kSrcDelta, go_on ? nullptr : c->delta, too));
   }
   c->have_phi = true;
   c->fields_at_pos = false;
@@ -690,6 +706,7 @@ pm_status pm_force(pm_ctx* c, const float* d_phi, const float* d_q, const void* 
   float fg = (float)(1.0 / a), fq = (float)(1.0 / (a * a));
   const bool one = use_q && combine_pays(c) && aligned16(phi) && aligned16(q);
   if (one) {
+    note_capture(c);
     PM_TRY(run_combine(c, phi, q, fg, fq));
     phi = combined(c);
     fg = 1.0f;
@@ -808,6 +825,7 @@ static pm_status step_impl(pm_ctx* c, void* d_pos, float* d_vel, const double* t
     if (c->p.comoving && !(times[s] > 0.0)) return PM_EINVAL;
     if (s > 0 && !(times[s] > times[s - 1])) return PM_EINVAL;
   }
+  note_capture(c);
   // A sort scatters the particles into the other of two buffers (the
   // caller's arrays and the workspace copies), which then becomes current;
   // the caller's arrays receive the state once, at the end of the call.
@@ -1210,6 +1228,7 @@ pm_status pm_spline_step(pm_ctx* c, void* d_pos, float* d_vel, const double* tim
     });
   };
   c->fields_at_pos = false;
+  note_capture(c);
   Kick close = {0.0, 0.0};
   for (int s = 0; s <= nsteps; ++s) {
     // fields at times[s]; the closing half-kick of step s - 1, then the
