@@ -357,21 +357,31 @@ pm_status sort_into(pm_ctx* c, const void* pos, const float* vel, const int32_t*
   return PM_OK;
 }
 
-// From this many particles on, positions in an order of the caller's are
-// binned by tile into the workspace for one deposit, which then runs from
-// LDS windows instead of adding to the mesh particle by particle (24 to 160
-// G adds/s, less where cells are dense).  Whole pm_deposit calls, direct
-// against binned: 256^3 in lattice order 1491 against 498 us, in clumps 4114
-// against 450; 128^3 250 against 83 and 775 against 91; 64^3 48 against 39.
-// Below, the six small launches cost more than they save for particles in
-// lattice order (32^3: 13 against 33 us) and about what they save in random
-// order (100003 at 64^3: 45 against 37).
+// Positions in an order of the caller's can be binned by tile into the
+// workspace for one deposit, which then runs from LDS windows instead of
+// adding to the mesh particle by particle (24 to 160 G adds/s, less where
+// cells are dense).  Whole pm_deposit calls, direct against binned: 256^3 in
+// lattice order 1491 against 498 us, in clumps 4114 against 450; 128^3 250
+// against 83 and 775 against 91; 64^3 48 against 39.  Below 2^17 the six small
+// launches cost more than they save for particles in lattice order (32^3: 13
+// against 33 us) and about what they save in random order (100003 at 64^3: 45
+// against 37).  Larger meshes pay for their tiles (counters, scans, a window
+// per tile) and take more: random order, direct against binned, 128^3 2^17
+// 67 against 89 us, 2^18 112 against 98; 256^3 2^18 158 against 177, 2^19 248
+// against 215; 512^3 2^19 888 against 967, 2^20 1078 against 996.
 constexpr int64_t kBinMin = 1 << 17;
+bool bin_pays(const pm_ctx* c) { return c->np >= std::max<int64_t>(kBinMin, 2048 * c->N); }
+// One binning for the four deposits of pm_kinetic_split.  Random order, direct
+// against binned: 128^3 2^17 310 against 236 us; 256^3 2^17 423 against 442,
+// 2^18 621 against 538; 512^3 2^19 2744 against 3027, 2^20 3623 against 3253.
+bool bin_pays_four(const pm_ctx* c) {
+  return c->np >= std::max<int64_t>(kBinMin, 16 * (int64_t)c->tiles);
+}
 
 // Deposit at pos, in the order of the tile map tm (null: in any order).
 pm_status run_deposit(pm_ctx* c, const void* pos, const TileMap* tm) {
   PM_TRY(timed(c, kcFill, [&] { return launch_fill_zero(c->mass, 8 * c->ncell + kStrayBytes, c->stream); }));
-  if (!tm && c->np >= kBinMin) {
+  if (!tm && bin_pays(c)) {
     PM_TRY(bin_into(c, c->bin_map, pos, nullptr, nullptr, c->pos_tmp, nullptr, nullptr));
     pos = c->pos_tmp;
     tm = &c->bin_map;
@@ -910,7 +920,7 @@ static pm_status step_impl(pm_ctx* c, void* d_pos, float* d_vel, const double* t
     gc.fd_units = drift(c->p, t0, t1) * fdu;
     // gather + kick + drift, fused with the deposit of the drifted particles
     // (unsorted, a large deposit is binned on its own)
-    const bool split = !c->sorted && !en && c->np >= kBinMin;
+    const bool split = !c->sorted && !en && bin_pays(c);
     if (!split)
       PM_TRY(timed(c, kcFill, [&] { return launch_fill_zero(c->mass, 8 * c->ncell + kStrayBytes, c->stream); }));
     // once the particles have moved since the sort, a state whose adaptive
@@ -1040,7 +1050,7 @@ pm_status pm_kinetic_split(pm_ctx* c, const void* d_pos, const float* d_vel, dou
   const TileMap* tm = c->sorted ? &c->tmap : nullptr;
   const void* pos = d_pos;
   const float* vel = d_vel;
-  if (!tm && c->np >= kBinMin) {
+  if (!tm && bin_pays_four(c)) {
     PM_TRY(bin_into(c, c->bin_map, d_pos, d_vel, nullptr, c->pos_tmp, c->vel_tmp, nullptr));
     tm = &c->bin_map;
     pos = c->pos_tmp;
@@ -1092,7 +1102,7 @@ pm_status pm_density_rms_diff(pm_ctx* c, const void* d_pos_a, const void* d_pos_
   // on a sorted context the tile map can describe one of the two states at
   // most: b is binned (read in the other state's order it took 1440 us at
   // 256^3 and 245 at 128^3, binned 145 + 252 and 35 + 44)
-  PM_TRY(run_deposit(c, d_pos_b, c->sorted && c->np < kBinMin ? &c->tmap : nullptr));
+  PM_TRY(run_deposit(c, d_pos_b, c->sorted && !bin_pays(c) ? &c->tmap : nullptr));
   PM_TRY(dev(hipMemcpyAsync(mass_b, c->mass, mesh_bytes, hipMemcpyDeviceToDevice, c->stream)));
   PM_TRY(run_deposit(c, d_pos_a));
   const int nb = diag_node_blocks(c);

@@ -71,3 +71,42 @@ def test_captured_calls_and_the_spectrum_of_the_deposit(pm, gpu):
         torch.cuda.synchronize()
         ctx.close()
         fresh.close()
+
+
+@pytest.mark.parametrize("n,least,least_four", [(32, 1 << 17, 1 << 17), (128, 1 << 18, 1 << 17),
+                                                (256, 1 << 19, 1 << 17)])
+def test_binning_by_particles_and_mesh(pm, gpu, n, least, least_four):
+    """An unsorted deposit is binned where the particles pay for the mesh's
+    tiles, on its own, within a step and for the four of the kinetic split
+    (route read from the kernels); the masses and states are bitwise the
+    sorted context's."""
+    import torch
+    for npart in (least_four - 1, least_four, least - 1, least):
+        st = _random(n, npart, npart)
+        lp = pm.make_params(n, npart, float(n), hbar_over_m=1e-3)
+        out = []
+        for order in (False, True):
+            ctx = pm.PMContext(lp, device=gpu)
+            pos, vel = to_device(st, gpu)
+            ids = torch.arange(npart, dtype=torch.int32, device=gpu)
+            if order:
+                ctx.sort(pos, vel, ids)
+            binned = []
+            ctx.timing(True)
+            split = ctx.kinetic_split(pos, vel)
+            binned.append("sort_count" in ctx.timing_read())
+            ctx.timing(True)
+            ctx.deposit(pos)
+            binned.append("sort_count" in ctx.timing_read())
+            mass = ctx.workspace[: 8 * n ** 3].view(torch.int64).clone()
+            ctx.timing(True)
+            ctx.step(pos, vel, [0.0, 1e-3])
+            binned.append("sort_count" in ctx.timing_read())
+            p, v = torch.empty_like(pos), torch.empty_like(vel)
+            p[:, ids.long()], v[:, ids.long()] = pos, vel
+            out.append((mass, p, v, split["K"]))
+            assert binned == ([False] * 3 if order
+                              else [npart >= least_four, npart >= least, npart >= least])
+            ctx.close()
+        assert all(torch.equal(a, b) for a, b in zip(out[0][:3], out[1][:3]))
+        assert abs(out[0][3] - out[1][3]) <= 1e-12 * out[1][3]
