@@ -65,16 +65,31 @@ __device__ __forceinline__ T& soa(T* base, int64_t np, int d, unsigned p) {
   return *reinterpret_cast<T*>(reinterpret_cast<B*>(base + d * np) + (p << 2));
 }
 
-// The position words and (VEL) velocity of particle p.
-template <bool VEL, typename P>
+// The position words and velocity of particle p: without the velocity, with
+// it, or with it where vel is not null.
+enum VelLoad : int { kNoVel, kVel, kVelTested };
+template <int VEL, typename P>
 __device__ __forceinline__ void load_particle(const void* __restrict__ pos,
                                               const float* __restrict__ vel, int64_t np, P p,
                                               uint32_t raw[3], float v[3]) {
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     raw[d] = soa(static_cast<const uint32_t*>(pos), np, d, p);
-    v[d] = VEL ? soa(vel, np, d, p) : 0.0f;
+    v[d] = VEL == kVel || (VEL == kVelTested && vel) ? soa(vel, np, d, p) : 0.0f;
   }
+}
+// Which load the untiled gather takes.  vel is never null where it is wanted,
+// but the test ends the loop body's first block there, and the compiler then
+// issues the nodes of two fields in larger groups (28 loads before the first
+// wait instead of 18): closing half-kick of 2^20 particles in random order at
+// 256^3 1059 -> 790 us, 512^3 1100 -> 778, with energies at 256^3, 2^23
+// particles, 7417 -> 5921 (push in the float form 6847 -> 5641).  With one
+// field, and in the float form's half-kick, it is the other way round (300
+// against 245 us, 905 against 712).
+template <bool FIXED, bool HAS_Q, int MODE, bool EN>
+constexpr int vel_load() {
+  if (MODE == kForce) return kNoVel;
+  return HAS_Q && (MODE == kKick ? FIXED : EN) ? kVelTested : kVel;
 }
 
 // Low 32 bits of rint(a * b), ties to even: the drift in fixed-point units,
@@ -229,7 +244,7 @@ __global__ void __launch_bounds__(kBlock) k_gather(void* __restrict__ pos,
     int ic[3];
     float f[3], xf[3], vin[3];
     uint32_t u[3], raw[3];
-    load_particle<MODE != kForce>(pos, vel, np, p, raw, vin);
+    load_particle<vel_load<FIXED, HAS_Q, MODE, EN>()>(pos, vel, np, p, raw, vin);
     decode_cell<LOGN, FIXED>(raw, ic, f, u, xf);
     auto node = [&](int a, int b, int c) {
       return ((size_t)((ic[0] + a - 1) & MASK) * N + ((ic[1] + b - 1) & MASK)) * N +
@@ -383,7 +398,7 @@ __global__ void __launch_bounds__(kGatherBlock, gather_waves(WIDE, EN && HAS_Q))
   uint32_t raw_n[3];
   float vin_n[3];
   unsigned p = lo + threadIdx.x;
-  if (p < hi) load_particle<true>(pos, vel, np, p, raw_n, vin_n);
+  if (p < hi) load_particle<kVel>(pos, vel, np, p, raw_n, vin_n);
   const int ox = (t / (NTY * NTZ)) * TX, oy = ((t / NTZ) % NTY) * TY, oz = (t % NTZ) * TZ;
   {
     // all of a thread's window loads are issued before the first is used
@@ -412,7 +427,7 @@ __global__ void __launch_bounds__(kGatherBlock, gather_waves(WIDE, EN && HAS_Q))
       raw[d] = raw_n[d];
       vin[d] = vin_n[d];
     }
-    if (p + kGatherBlock < hi) load_particle<true>(pos, vel, np, p + kGatherBlock, raw_n, vin_n);
+    if (p + kGatherBlock < hi) load_particle<kVel>(pos, vel, np, p + kGatherBlock, raw_n, vin_n);
     decode_cell<LOGN, FIXED>(raw, ic, f, u, xf);
     const int rx = (ic[0] - ox + HG) & MASK, ry = (ic[1] - oy + HG) & MASK,
               rz = (ic[2] - oz + HG) & MASK;
@@ -473,7 +488,7 @@ __global__ void __launch_bounds__(kGatherBlock, gather_waves(WIDE, EN && HAS_Q))
     for (int c = threadIdx.x; c < (int)(kD / 16); c += kGatherBlock)
       reinterpret_cast<uint4*>(lds)[c] = make_uint4(0u, 0u, 0u, 0u);
     p = lo + threadIdx.x;
-    if (p < hi) load_particle<false>(pos, vel, np, p, raw_n, vin_n);
+    if (p < hi) load_particle<kNoVel>(pos, vel, np, p, raw_n, vin_n);
     __syncthreads();
     T* mass = static_cast<T*>(mass_v);
     unsigned my_stray = 0;   // this thread's deposits outside the narrow window
@@ -482,7 +497,7 @@ __global__ void __launch_bounds__(kGatherBlock, gather_waves(WIDE, EN && HAS_Q))
 #pragma unroll
       for (int d = 0; d < 3; ++d) raw[d] = raw_n[d];
       if (p + kGatherBlock < hi)
-        load_particle<false>(pos, vel, np, p + kGatherBlock, raw_n, vin_n);
+        load_particle<kNoVel>(pos, vel, np, p + kGatherBlock, raw_n, vin_n);
       // natural corner order (consecutive lanes of a wave add to neighbouring
       // cells together); the fixed-point remainder d goes to the heaviest
       // corner in a ninth add where it is not zero

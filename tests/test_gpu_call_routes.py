@@ -171,3 +171,25 @@ def test_empty_cells_share_the_floor_s_root(pm, gpu):
         us.append(best * 1e3)
         ctx.close()
     assert us[0] <= 2.25 * us[1], us
+
+
+def test_closing_half_kick_of_few_particles(pm, gpu):
+    """Too few unsorted particles for one combined potential: the half-kick
+    reads two fields, for about three times the cost of one (4.3 with the
+    loads in small groups)."""
+    import torch
+    n, npart = 256, 1 << 20
+    pos, vel = to_device(_random(n, npart, 6), gpu)
+    us = []
+    for hm in (0.0, 1e-6):
+        ctx = pm.PMContext(pm.make_params(n, npart, float(n), hbar_over_m=hm), device=gpu)
+        best = float("inf")
+        for _ in range(6):
+            ctx.timing(True)
+            ctx.step(pos, vel, [0.0, 1e-30])
+            kernels = ctx.timing_read()
+            assert "combine" not in kernels
+            best = min(best, kernels["kick"][1])
+        us.append(best * 1e3)
+        ctx.close()
+    assert us[1] <= 3.7 * us[0], us
