@@ -1093,18 +1093,42 @@ pm_status pm_kinetic_split(pm_ctx* c, const void* d_pos, const float* d_vel, dou
   return PM_OK;
 }
 
+constexpr int64_t kSampleMin = 1 << 21;
 pm_status pm_density_rms_diff(pm_ctx* c, const void* d_pos_a, const void* d_pos_b,
                               double* rms, int64_t* cells) {
   if (!c || !d_pos_a || !d_pos_b || !rms || !cells) return PM_EINVAL;
   // the reference state's mass mesh is kept in delta..phi (8 N^3 bytes)
   void* mass_b = c->delta;
   const size_t mesh_bytes = (c->fixed ? 8 : 4) * c->ncell;
-  // on a sorted context the tile map can describe one of the two states at
-  // most: b is binned (read in the other state's order it took 1440 us at
-  // 256^3 and 245 at 128^3, binned 145 + 252 and 35 + 44)
-  PM_TRY(run_deposit(c, d_pos_b, c->sorted && !bin_pays(c) ? &c->tmap : nullptr));
+  // A sorted context's tile map may describe either state, both (a later
+  // snapshot of the sorted particles) or none.  With many particles a sample
+  // of each decides; from one missing particle in sixteen on binning costs
+  // less (256^3 lattice order, one deposit: own order 145 us, binned 145 + 252,
+  // foreign 3400; whole calls, both own 774 -> 634 us, a foreign 4127 -> 912).
+  // Its copy and wait take 28 us; up to 2^21 particles b is taken for foreign
+  // instead (128^3 166 us, sampled 198; both own 142 from the tiles).
+  const TileMap *tm_a = c->sorted ? &c->tmap : nullptr, *tm_b = tm_a;
+  if (c->sorted && c->np <= kSampleMin) {
+    if (bin_pays(c)) tm_b = nullptr;
+  } else if (c->sorted && bin_pays(c)) {
+    unsigned n[4 * kSampleBlocks];
+    unsigned* d_n = reinterpret_cast<unsigned*>(c->partials);
+    PM_TRY(timed(c, kcSortCount, [&] {
+      return launch_map_misses(c->fixed, d_pos_a, d_pos_b, c->np, c->logn, c->tmap, d_n, c->stream);
+    }));
+    PM_TRY(dev(hipMemcpyAsync(n, d_n, sizeof(n), hipMemcpyDeviceToHost, c->stream)));
+    PM_TRY(dev(hipStreamSynchronize(c->stream)));
+    unsigned missed[2] = {0, 0}, sampled[2] = {0, 0};
+    for (int k = 0; k < 2 * kSampleBlocks; ++k) {
+      missed[k / kSampleBlocks] += n[2 * k];
+      sampled[k / kSampleBlocks] += n[2 * k + 1];
+    }
+    if (16 * missed[0] > sampled[0]) tm_a = nullptr;
+    if (16 * missed[1] > sampled[1]) tm_b = nullptr;
+  }
+  PM_TRY(run_deposit(c, d_pos_b, tm_b));
   PM_TRY(dev(hipMemcpyAsync(mass_b, c->mass, mesh_bytes, hipMemcpyDeviceToDevice, c->stream)));
-  PM_TRY(run_deposit(c, d_pos_a));
+  PM_TRY(run_deposit(c, d_pos_a, tm_a));
   const int nb = diag_node_blocks(c);
   PM_TRY(timed(c, kcDiagNodes, [&] {
     return launch_rel_diff_nodes(c->fixed, c->mass, mass_b, (int64_t)c->ncell, c->partials, nb,

@@ -260,6 +260,11 @@ hipError_t launch_sort_scatter(const void* pos, const float* vel, const int* ids
                                const unsigned* key, const unsigned* rank,
                                const unsigned* slice_start, uint32_t* pos_out, float* vel_out,
                                int* ids_out, hipStream_t s, const Batch& bt = Batch());
+// Samples of two states against a tile map: (missed, sampled) for each block
+// of a, then of b, in out[4 * kSampleBlocks].
+constexpr int kSampleBlocks = 128;
+hipError_t launch_map_misses(bool fixed, const void* pos_a, const void* pos_b, int64_t np,
+                             int logn, const TileMap& tm, unsigned* out, hipStream_t s);
 hipError_t launch_sort_copy(uint32_t* pos, float* vel, const uint32_t* pos_tmp,
                             const float* vel_tmp, int64_t np, hipStream_t s, const Batch& bt);
 

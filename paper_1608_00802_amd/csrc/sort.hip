@@ -375,4 +375,50 @@ hipError_t launch_sort_copy(uint32_t* pos, float* vel, const uint32_t* pos_tmp,
   return hipGetLastError();
 }
 
+// Particles sampled from the chunks of a tile map (the first of every
+// blockIdx.x-th part of them) and those whose deposit would miss the tile's
+// window, per block: (missed, sampled) at out[2 (blockIdx.y grid + blockIdx.x)].
+template <bool FIXED>
+__global__ void __launch_bounds__(kBlock) k_map_misses(const void* __restrict__ pos_a,
+                                                       const void* __restrict__ pos_b, int64_t np,
+                                                       int logn, TileMap tm,
+                                                       unsigned* __restrict__ out) {
+  const void* pos = blockIdx.y ? pos_b : pos_a;
+  const unsigned used = tm.used[0];
+  bool in = false, miss = false;
+  if (used > 0) {
+    const uint4 c = tm.chunks[(unsigned)((unsigned long long)blockIdx.x * used / gridDim.x)];
+    const unsigned p = c.y + threadIdx.x;
+    in = p < c.z;
+    if (in) {
+      const int tile = (int)c.x, lz = tile_lz(logn), ntz = logn - lz, nty = logn - kTileLY;
+      const int mask = (1 << logn) - 1;
+      const int o[3] = {(tile >> (nty + ntz)) << kTileLX,
+                        ((tile >> ntz) & ((1 << nty) - 1)) << kTileLY,
+                        (tile & ((1 << ntz) - 1)) << lz};
+      const int t[3] = {1 << kTileLX, 1 << kTileLY, 1 << lz};
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+        miss = miss || ((cell_of<FIXED>(pos, np, p, d, logn) - o[d] + kDepHalo) & mask) >=
+                           t[d] + 2 * kDepHalo;
+    }
+  }
+  const int missed = __syncthreads_count(miss), sampled = __syncthreads_count(in);
+  if (threadIdx.x == 0) {
+    unsigned* o = out + 2 * (blockIdx.y * gridDim.x + blockIdx.x);
+    o[0] = (unsigned)missed;
+    o[1] = (unsigned)sampled;
+  }
+}
+
+hipError_t launch_map_misses(bool fixed, const void* pos_a, const void* pos_b, int64_t np,
+                             int logn, const TileMap& tm, unsigned* out, hipStream_t s) {
+  const dim3 g(kSampleBlocks, 2);
+  if (fixed)
+    hipLaunchKernelGGL(k_map_misses<true>, g, dim3(kBlock), 0, s, pos_a, pos_b, np, logn, tm, out);
+  else
+    hipLaunchKernelGGL(k_map_misses<false>, g, dim3(kBlock), 0, s, pos_a, pos_b, np, logn, tm, out);
+  return hipGetLastError();
+}
+
 }  // namespace fdm

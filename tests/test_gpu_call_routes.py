@@ -193,3 +193,31 @@ def test_closing_half_kick_of_few_particles(pm, gpu):
         us.append(best * 1e3)
         ctx.close()
     assert us[1] <= 3.7 * us[0], us
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("n,npart", [(32, (1 << 17) - 1), (32, 1 << 17), (128, 1 << 21),
+                                     (128, (1 << 21) + 77), (256, 3000001)])
+def test_density_difference_by_the_order_of_each_state(pm, gpu, n, npart, prec):
+    """On a sorted context: with many particles a state is binned where it is
+    not in the order of the sort and read from its tiles where it is; below,
+    b is binned, or nothing (route from the number of binnings).  The
+    difference is the unsorted context's."""
+    import torch
+    lp = pm.make_params(n, npart, float(n), precision=prec)
+    ctx, plain = pm.PMContext(lp, device=gpu), pm.PMContext(lp, device=gpu)
+    own, vel = to_device(_random(n, npart, 1), gpu, fp32_positions=prec == 0)
+    ctx.sort(own, vel)
+    near = own.clone()        # a snapshot a little later
+    near += (1 << 20) if prec else 1e-3
+    other, _ = to_device(_random(n, npart, 2), gpu, fp32_positions=prec == 0)
+    for a, b, foreign in ((own, near, 0), (own, other, 1), (other, own, 1), (other, other, 2)):
+        rms, cells = plain.density_rms_diff(a, b)
+        ctx.timing(True)
+        got, got_cells = ctx.density_rms_diff(a, b)
+        kernels = ctx.timing_read()
+        want = foreign if npart > 1 << 21 else int(npart >= 1 << 17)
+        assert kernels.get("sort_scatter", (0, 0))[0] == want
+        assert got_cells == cells
+        # (float sums of the density in another order: 2^-20 of it, a node)
+        assert abs(got - rms) <= (0.0 if prec else 1e-3) * rms + (1e-12 * rms if prec else 1e-5)
