@@ -517,6 +517,39 @@ __global__ void __launch_bounds__(kBlock) k_spline_qforce_fixed_reach(
   }
 }
 
+// One particle's force by a whole wave, as each_node_wave (the lanes' sums w
+// are still to be added up): Q is loaded inside the support only, and all of a
+// column's nodes before the first is used.
+template <int H2>
+__device__ __forceinline__ void wave_force(int logn, const int i[3], const float f[3],
+                                           float inv_h, const float* __restrict__ qmesh,
+                                           float w[3]) {
+  using Rc = Reach<H2>;
+  const int mask = (1 << logn) - 1;
+  w[0] = w[1] = w[2] = 0.0f;
+  for (int col = threadIdx.x & 63; col < Rc::SPAN * Rc::SPAN; col += 64) {
+    const int a = col / Rc::SPAN - Rc::R, b = col % Rc::SPAN - Rc::R;
+    const float dx = scaled(a, f[0], inv_h), dy = scaled(b, f[1], inv_h);
+    const float dxy2 = square(dx) + square(dy);
+    const int row = ((((i[0] + a) & mask) << logn) + ((i[1] + b) & mask)) << logn;
+    float q[Rc::SPAN];
+#pragma unroll
+    for (int k = 0; k < Rc::SPAN; ++k) {
+      const float s = dxy2 + square(scaled(k - Rc::R, f[2], inv_h));
+      q[k] = 0.0f;
+      if (s <= 1.0f && s != 0.0f) q[k] = qmesh[row + ((i[2] + k - Rc::R) & mask)];
+    }
+#pragma unroll
+    for (int k = 0; k < Rc::SPAN; ++k) {
+      const float dz = scaled(k - Rc::R, f[2], inv_h);
+      const float t = q[k] * spline_g<true>(dxy2 + square(dz));
+      w[0] = fmaf(t, dx, w[0]);
+      w[1] = fmaf(t, dy, w[1]);
+      w[2] = fmaf(t, dz, w[2]);
+    }
+  }
+}
+
 // The factors of one pass of the spline step over the particles: the closing
 // half-kick of the previous step, the opening one of the next and its drift.
 struct SplineStep {
@@ -608,15 +641,8 @@ __global__ void __launch_bounds__(kSplineBlock, H2 <= 7 && !STEP ? 8 : 5) k_spli
       }
       if (own) own_force(sp.logn, i, f, h, inv_h, -Reach<H2>::R, Reach<H2>::R + 1, qmesh, g);
       each_lane(at < 0 && !lane_own, i, f, [&](int lane, const int iu[3], const float fu[3]) {
-        float w[3] = {0.0f, 0.0f, 0.0f};
-        each_node_wave<H2>(sp.logn, iu, fu, inv_h,
-                           [&](int node, float x, float y, float z, float s) {
-          if (s > 1.0f || s == 0.0f) return;
-          const float t = qmesh[node] * spline_g<true>(s);
-          w[0] = fmaf(t, x, w[0]);
-          w[1] = fmaf(t, y, w[1]);
-          w[2] = fmaf(t, z, w[2]);
-        });
+        float w[3];
+        wave_force<H2>(sp.logn, iu, fu, inv_h, qmesh, w);
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
           for (int off = 32; off > 0; off >>= 1) w[d] += __shfl_xor(w[d], off, 64);
