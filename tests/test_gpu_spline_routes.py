@@ -203,3 +203,42 @@ def test_positions_that_were_not_the_sorted_ones(pm, gpu):
     assert float((out[0][1] - out[1][1]).abs().max()) <= 300 * 2.0 ** -24 * 8 * scale
     assert out[1][2][0] <= 1.25 * out[0][2][0]
     assert out[1][2][1] <= 3.0 * out[0][2][1]
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("n,npart,h,moved", [(16, 20001, 2.0, 1.0), (32, 40001, 3.5, 0.5),
+                                             (64, 120001, 5.0, 3.0), (64, 120001, 3.5, 20.0)])
+def test_push_of_dense_tiles_and_strays(pm, gpu, n, npart, h, moved, prec):
+    """The fused step where tiles hold several pieces and particles have left
+    theirs (by a wave each, near or far; by their lanes where many are far),
+    against the separate kernels.  Each force is a sum of up to 600 terms
+    rounded in another order, whose magnitudes may exceed their sum's by 8."""
+    import torch
+    rng = np.random.default_rng(npart)
+    x = rng.random((npart, 3)) * n
+    x[: npart // 2] = 9.0 + 5.0 * rng.random((npart // 2, 3))       # one dense tile
+    first = quantize_state(x, np.zeros((npart, 3)), n, {})
+    st = quantize_state((x + moved * rng.standard_normal((npart, 3))) % n,
+                        0.05 * rng.standard_normal((npart, 3)), n, {})
+    lp = pm.make_params(n, npart, float(n), hbar_over_m=0.05, precision=prec)
+    out = []
+    for fused in (False, True):
+        ctx = pm.PMContext(lp, device=gpu)
+        pos, vel = to_device(st, gpu, fp32_positions=prec == 0)
+        ids = torch.arange(npart, dtype=torch.int32, device=gpu)
+        if fused:
+            sorted_pos, sorted_vel = to_device(first, gpu, fp32_positions=prec == 0)
+            ctx.sort(sorted_pos, sorted_vel, ids)
+            pos, vel = pos[:, ids.long()].contiguous(), vel[:, ids.long()].contiguous()
+        ctx.timing(True)
+        ctx.spline_step(pos, vel, [0.0, 0.01, 0.02], h)
+        assert ("force" in ctx.timing_read()) == (not fused)
+        p, v = torch.empty_like(pos), torch.empty_like(vel)
+        p[:, ids.long()], v[:, ids.long()] = pos, vel
+        cells = (p.long() & 0xffffffff).double() * (n / 2.0 ** 32) if prec else p.double()
+        out.append((cells, v.double()))
+    kick = float((out[0][1] - torch.from_numpy(st.vel32.astype(np.float64)).to(gpu)).abs().max())
+    bound = 600 * 2.0 ** -24 * 8 * kick + 2.0 ** -22
+    assert float((out[1][1] - out[0][1]).abs().max()) <= bound
+    d = (out[1][0] - out[0][0] + n / 2) % n - n / 2
+    assert float(d.abs().max()) <= 0.02 * bound + 2.0 ** -22 * n
