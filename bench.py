@@ -197,7 +197,7 @@ def spline_section(st, n, box, steps=5, warmup=2, h=3.5):
     kern = ctx.timing_read()
     ctx.timing(False)
     out = {"form": "pm_spline_step: spline density (h = 3.5 cells) for gravity and Q, "
-                   "kernel-gradient Q force, unfused KDK",
+                   "kernel-gradient Q force, forces, kicks and drift in one pass",
            "value": st.npart * steps / wall, "ms_per_step": wall * 1e3 / steps,
            "finite": bool(torch.isfinite(vel).all().item()),
            "kernels": {k: {"launches": v[0], "avg_ms": round(v[1] / v[0], 4)}

@@ -488,8 +488,10 @@ pm_status run_fields(pm_ctx* c, const void* pos, bool energy, bool deposit = tru
 // one pass over the cells that forms fg phi + fq Q first (in the spectrum's
 // place, free between solves, which is larger than a mesh) halves those reads.
 // pm_force calls: 256^3 in lattice order 514 -> 310 us, in clumps 1022 -> 527;
-// 600001 random particles at 128^3 394 -> 97; 64^3 15 -> 11; 32^3, where the
-// extra launch shows, 5.6 against 8.4.  With far fewer particles than cells
+// 600001 random particles at 128^3 394 -> 97; 64^3 15 -> 11; 32768 at 32^3,
+// where the extra launch shows, 5.6 against 8.4, 65537 there 7.5 against 10.8
+// in lattice order and 17 against 11 in clumps.  With far fewer particles than
+// cells
 // the pass (12 bytes per cell) costs more than particles in order gain.
 constexpr int64_t kCombineMin = 1 << 16;
 bool combine_pays(const pm_ctx* c) {

@@ -640,8 +640,9 @@ struct QTiles {
 // but for cells without mass, all at the floor, whose root is formed once (a
 // wave whose cells are all empty skips the others: 256^3, 80 % of the
 // particles in 400 clumps, 130 -> 121 us, 2^20 particles 128 -> 120, where the
-// pass and the stencil took 122 and 118; 512^3, 2^17 to 2^23 particles, 1139
-// -> 912 to 1067, the two 863).
+// pass and the stencil took 122 and 118; the box evolved to a = 0.5 129 ->
+// 124, the two 129; 512^3, 2^17 to 2^23 particles, 1139 -> 912 to 1067, the
+// two 863).
 template <int LOGN, bool FIXED, int OUT>
 __global__ void __launch_bounds__(QTiles<1 << LOGN>::NT) k_c2r_q(const float2* __restrict__ spec,
                                                   const float2* __restrict__ tw,

@@ -334,8 +334,8 @@ struct Window {
 // with a gather window that is wider by HG cells on each side: 302 -> 271
 // us per launch over the 24 steps after a sort of a 256^3 field (1 cell rms
 // from the lattice, 0.02 cells per step), 354 -> 329 us on clumps over an
-// empty background, and 321 -> 209 us for the closing half-kick.  What bounds
-// it: phase 1 alone takes 192 us, 4.5 TB/s of particle traffic where a copy
+// empty background (on the box evolved to a = 0.5, 355 -> 359), and 321 -> 209
+// us for the closing half-kick (evolved 429 -> 259).  What bounds it: phase 1 alone takes 192 us, 4.5 TB/s of particle traffic where a copy
 // reaches 5.1; the window flush, one u64 atomic per non-zero cell (2.07 per
 // mesh cell), 53 us; the weights and LDS adds 24 us.
 // WIDE: one cell more of halo in both windows, for steps whose particles have

@@ -97,7 +97,7 @@ constexpr unsigned long long kUnitMask = 0x000FFFFFFFFFFFFFull;
 // h <= H2 / 2.  Along x and y the particle's fraction is folded into
 // [0, 1/2] (offset o of a folded axis is node 1 - o), along z it is in
 // [0, 1); the smallest distance over the fraction's range decides.  For
-// h <= 3.5 these are 264 nodes on 43 rows, of which 180 are inside on
+// h <= 3.5 these are 256 nodes on 43 rows, of which 180 are inside on
 // average; the kernel is zero on the others.  All lanes of a wave run the
 // same nodes: per-particle spans visited fewer (a wave about 290 all the
 // same, the longest of its lanes' spans), at 45 instructions each.
@@ -274,7 +274,8 @@ __device__ __forceinline__ void each_lane(bool which, const int i[3], const floa
 // with every node of theirs added to the mesh (1.35 right after it).
 // Each add carries the bits of 2^52 on top of its integer; they only reach
 // bits 52 and up, which the flush drops: a piece's sum at a node stays below
-// 2^52 (kSplinePiece particles of at most 8 / (pi h^3) < 0.32 each, in 2^-40).
+// 2^52 (at most 3/2 kPiece particles of at most 8 / (pi h^3) < 0.32 each, in
+// 2^-40).
 //
 // What bounds it is the kernel arithmetic (8 to 12 instructions per node) and
 // the LDS adds (11 cycles per wave instruction at scattered addresses): 1.4
@@ -283,6 +284,7 @@ __device__ __forceinline__ void each_lane(bool which, const int i[3], const floa
 // against 0.99 ms.  512 threads per block (1.53 ms with all nodes of the
 // particles out of their tile on the mesh): 256 take 1.74 ms, 1024 1.56.
 constexpr int kSplineBlock = 512;
+static_assert(3 * kPiece / 2 * 32 / 100 < (1u << (52 - kMassShift)), "a piece's sum at a node");
 constexpr int kSplineGrid = 4096;
 constexpr int kSplineH2Max = 10;   // the widest window: h <= 5
 template <int H2>
