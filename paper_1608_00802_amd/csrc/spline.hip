@@ -588,8 +588,13 @@ __device__ __forceinline__ uint32_t spline_drift(const SplinePos& sp, uint32_t r
 // STEP: also -grad phi from its own window, the kicks and the drift, so that
 // the particles' traffic (60 bytes each) runs under the arithmetic
 // (256^3, h = 3.5: 1.48 ms in place of 1.18 and 0.54 for the separate passes).
+// Waves per SIMD, which set the register budget: four blocks per CU for the
+// force up to h = 3.5, three for the step up to h = 2.5 (held to 80 registers;
+// at 86, two blocks, two steps at 128^3 and h = 2 take 541 us instead of 520),
+// two where the windows leave no room for more.
+constexpr int force_waves(int h2, bool step) { return step ? (h2 <= 5 ? 6 : 5) : h2 <= 7 ? 8 : 5; }
 template <int H2, bool STEP>
-__global__ void __launch_bounds__(kSplineBlock, H2 <= 7 && !STEP ? 8 : 5) k_spline_qforce_tiled(
+__global__ void __launch_bounds__(kSplineBlock, force_waves(H2, STEP)) k_spline_qforce_tiled(
     uint32_t* __restrict__ pos, int64_t np, SplinePos sp, TileMap tm,
     const float* __restrict__ qmesh, float h, float inv_h, float coef, float* __restrict__ acc,
     SplineStep st) {
