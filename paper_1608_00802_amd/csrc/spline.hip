@@ -452,8 +452,11 @@ __device__ __forceinline__ void own_force(int logn, const int i[3], const float 
                                           const float* __restrict__ qmesh, float g[3]) {
   g[0] = g[1] = g[2] = 0.0f;
   each_node(logn, i, f, h, inv_h, lo, hi, [&](int node, float x, float y, float z, float s) {
-    if (s > 1.0f || s == 0.0f) return;
-    const float v = qmesh[node] * spline_g<true>(s);
+    float q = 0.0f;
+    if (!(s > 1.0f || s == 0.0f))
+      q = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(qmesh) +
+                                          ((uint32_t)node << 2));
+    const float v = q * spline_g<true>(s);
     g[0] = fmaf(v, x, g[0]);
     g[1] = fmaf(v, y, g[1]);
     g[2] = fmaf(v, z, g[2]);
