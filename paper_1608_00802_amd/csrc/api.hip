@@ -366,11 +366,18 @@ pm_status sort_into(pm_ctx* c, const void* pos, const float* vel, const int32_t*
 // launches cost more than they save for particles in lattice order (32^3: 13
 // against 33 us) and about what they save in random order (100003 at 64^3: 45
 // against 37).  Larger meshes pay for their tiles (counters, scans, a window
-// per tile) and take more: random order, direct against binned, 128^3 2^17
-// 67 against 89 us, 2^18 112 against 98; 256^3 2^18 158 against 177, 2^19 248
-// against 215; 512^3 2^19 888 against 967, 2^20 1078 against 996.
+// per tile): direct against binned in random and in lattice order, 128^3
+// 1024 N 67 and 56 against 89 and 59 us, 1536 N 90 and 72 against 94 and 63;
+// 256^3 1536 N 203 and 182 against 195 and 154; 512^3 1536 N 984 and 910
+// against 980 and 916.
 constexpr int64_t kBinMin = 1 << 17;
-bool bin_pays(const pm_ctx* c) { return c->np >= std::max<int64_t>(kBinMin, 2048 * c->N); }
+bool bin_pays(const pm_ctx* c) { return c->np >= std::max<int64_t>(kBinMin, 1536 * c->N); }
+// A step that bins pushes without depositing and reads the drifted positions
+// once more, so its line is higher.  Four steps, fused against binned, in
+// random and in lattice order: 128^3 1536 N 708 and 522 against 737 and 487 us,
+// 2048 N 857 and 600 against 796 and 501; 256^3 2048 N 2232 and 1652 against
+// 2212 and 1464; 512^3 2048 N 11076 and 9770 against 10929 and 9750.
+bool bin_pays_step(const pm_ctx* c) { return c->np >= std::max<int64_t>(kBinMin, 2048 * c->N); }
 // One binning for the four deposits of pm_kinetic_split.  Random order, direct
 // against binned: 128^3 2^17 310 against 236 us; 256^3 2^17 423 against 442,
 // 2^18 621 against 538; 512^3 2^19 2744 against 3027, 2^20 3623 against 3253.
@@ -922,7 +929,7 @@ static pm_status step_impl(pm_ctx* c, void* d_pos, float* d_vel, const double* t
     gc.fd_units = drift(c->p, t0, t1) * fdu;
     // gather + kick + drift, fused with the deposit of the drifted particles
     // (unsorted, a large deposit is binned on its own)
-    const bool split = !c->sorted && !en && bin_pays(c);
+    const bool split = !c->sorted && !en && bin_pays_step(c);
     if (!split)
       PM_TRY(timed(c, kcFill, [&] { return launch_fill_zero(c->mass, 8 * c->ncell + kStrayBytes, c->stream); }));
     // once the particles have moved since the sort, a state whose adaptive

@@ -73,15 +73,16 @@ def test_captured_calls_and_the_spectrum_of_the_deposit(pm, gpu):
         fresh.close()
 
 
-@pytest.mark.parametrize("n,least,least_four", [(32, 1 << 17, 1 << 17), (128, 1 << 18, 1 << 17),
-                                                (256, 1 << 19, 1 << 17)])
-def test_binning_by_particles_and_mesh(pm, gpu, n, least, least_four):
+@pytest.mark.parametrize("n,least,least_step,least_four",
+                         [(32, 1 << 17, 1 << 17, 1 << 17), (128, 3 << 16, 1 << 18, 1 << 17),
+                          (256, 3 << 17, 1 << 19, 1 << 17)])
+def test_binning_by_particles_and_mesh(pm, gpu, n, least, least_step, least_four):
     """An unsorted deposit is binned where the particles pay for the mesh's
     tiles, on its own, within a step and for the four of the kinetic split
     (route read from the kernels); the masses and states are bitwise the
     sorted context's."""
     import torch
-    for npart in (least_four - 1, least_four, least - 1, least):
+    for npart in (least_four - 1, least_four, least - 1, least, least_step - 1, least_step):
         st = _random(n, npart, npart)
         lp = pm.make_params(n, npart, float(n), hbar_over_m=1e-3)
         out = []
@@ -100,13 +101,14 @@ def test_binning_by_particles_and_mesh(pm, gpu, n, least, least_four):
             binned.append("sort_count" in ctx.timing_read())
             mass = ctx.workspace[: 8 * n ** 3].view(torch.int64).clone()
             ctx.timing(True)
-            ctx.step(pos, vel, [0.0, 1e-3])
-            binned.append("sort_count" in ctx.timing_read())
+            ctx.step(pos, vel, [0.0, 1e-3])     # two deposits: the opening one and the step's
+            binned.append(ctx.timing_read().get("sort_count", (0,))[0])
             p, v = torch.empty_like(pos), torch.empty_like(vel)
             p[:, ids.long()], v[:, ids.long()] = pos, vel
             out.append((mass, p, v, split["K"]))
-            assert binned == ([False] * 3 if order
-                              else [npart >= least_four, npart >= least, npart >= least])
+            assert binned == ([False, False, 0] if order
+                              else [npart >= least_four, npart >= least,
+                                    (npart >= least) + (npart >= least_step)])
             ctx.close()
         assert all(torch.equal(a, b) for a, b in zip(out[0][:3], out[1][:3]))
         assert abs(out[0][3] - out[1][3]) <= 1e-12 * out[1][3]
